@@ -204,7 +204,7 @@ avm_status avm_gas_create(int32_t device, double e_max_eV, int32_t n_bins, doubl
     d.kind = x.kind;
     d.angular = x.kind == AVM_CH_ELASTIC ? x.angular : 0;
     d.split = x.kind == AVM_CH_IONISATION ? x.split : 0;
-    d.loss = x.loss_eV;
+    d.loss = x.kind == AVM_CH_ELASTIC ? 0.0 : x.loss_eV;
     d.e_lo = x.e_lo_eV;
     d.e_hi = x.e_hi_eV;
     const double mu = x.kind == AVM_CH_ELASTIC ? x.mass_ratio : 0.0;
@@ -214,7 +214,8 @@ avm_status avm_gas_create(int32_t device, double e_max_eV, int32_t n_bins, doubl
     d.two_mu = 2.0 * mu;
     d.split_w = x.split_w_eV;
     d.atan_scale = x.split_w_eV > 0.0 ? 1.0 / (2.0 * x.split_w_eV) : 0.0;
-    d.inv_screen8 = x.screening_eV > 0.0 ? 8.0 / x.screening_eV : 0.0;
+    // (isotropic scattering: the screened form with 1/eta = 0)
+    d.inv_screen8 = d.angular && x.screening_eV > 0.0 ? 8.0 / x.screening_eV : 0.0;
     ChanP<float>& q = cf[c];
     q.kind = d.kind;
     q.angular = d.angular;
@@ -513,6 +514,12 @@ avm_status avm_field_slab(int32_t device, double z_lo_cm, double z_hi_cm, uint32
   D.n_E = n_E;
   D.z_lo = z_lo_cm;
   D.z_hi = z_hi_cm;
+  // the flight filter's half width, less a margin that covers the rounding
+  // of a flight's positions (double, and displacements in single precision)
+  const double half = 0.5 * (z_hi_cm - z_lo_cm), coord = std::fabs(z_lo_cm) + std::fabs(z_hi_cm);
+  D.z_mid = z_lo_cm + half;
+  D.z_half = half - (1e-9 * half + 1e-11 * coord);
+  D.z_half_f = half - (1e-5 * half + 1e-11 * coord);
   D.E = f->E;
   set_bfield(f, B_T);
   *out = f;

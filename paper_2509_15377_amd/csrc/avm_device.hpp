@@ -41,11 +41,6 @@
 #define AVM_FN __device__ __forceinline__
 #endif
 
-// Channel search: 2 (binary) or 4 (four-way steps, then binary).
-#ifndef AVM_SEARCH_WAYS
-#define AVM_SEARCH_WAYS 2
-#endif
-
 namespace avm {
 
 // electron status codes (non-zero: terminated)
@@ -113,7 +108,8 @@ template <class R>
 struct TabView {
   const R* tot;
   const R* cum0;
-  int32_t n_lo;
+  R x_lo;     // energies below x_lo bins have both nodes in tot and cum0 (n_lo - 1)
+  bool el0;   // channel 0 is elastic and acts at every energy
   const R* bgam;
   const R* binv;
   const R* bedge;
@@ -141,7 +137,8 @@ template <class R>
 struct TabLds {
   const AVM_LDS R* tot;
   const AVM_LDS R* cum0;
-  int32_t n_lo;
+  R x_lo;
+  bool el0;
   const AVM_LDS R* bgam;
   const AVM_LDS R* binv;
   const AVM_LDS R* bedge;
@@ -153,12 +150,14 @@ struct TabLds {
 // kernel's kFit instances): the accessors read them without an index test.
 // With the per-lane test each read carries a divergent global path, and the
 // waits the compiler places where the two paths join also hold up the LDS
-// reads that follow.
+// reads that follow.  bedge[-1] is -infinity and the last band's edge NaN
+// here, so that a comparison with an edge that does not exist is false.
 template <class R>
 struct TabFit {
   const AVM_LDS R* tot;
   const AVM_LDS R* cum0;
-  int32_t n_lo;
+  R x_lo;
+  bool el0;
   const AVM_LDS R* bgam;
   const AVM_LDS R* binv;
   const AVM_LDS R* bedge;
@@ -172,6 +171,8 @@ struct FieldDev {
   int32_t kind;
   uint32_t n_E;
   double z_lo, z_hi;
+  double z_mid;             // slab: middle; half width less a margin, by precision (slab_clear)
+  double z_half, z_half_f;
   const double* E;          // slab: [n_E][3]
   double a, b, a2, b2;      // polar: wire and tube radii (and squares)
   double inv_dlog;          // (n_r - 1) / ln(b/a)
@@ -451,6 +452,7 @@ template <> struct M<double> {
   // and emission angles, speeds): the accurate ones in FP64
   AVM_FN static double log_s(double x) { return log_pos(x); }
   AVM_FN static double sqrt_s(double x) { return sqrt_nn(x); }
+  AVM_FN static double sqrt_0(double x) { return sqrt_nn(x); }  // 0 for x <= 0
   AVM_FN static double rsqrt_s(double x) { return rsqrt_pos(x); }
 };
 template <> struct M<float> {
@@ -465,6 +467,10 @@ template <> struct M<float> {
   AVM_FN static void sincospi_(float x, float* s, float* c) { sincospif(x, s, c); }
   AVM_FN static float abs_(float x) { return fabsf(x); }
   AVM_FN static float inf() { return __builtin_inff(); }
+  AVM_FN static float sqrt_0(float x) {  // sqrt_s, 0 for x <= 0
+    const float r = sqrt_s(x);
+    return x > 0.0f ? r : 0.0f;
+  }
   // the sampling and scattering forms in FP32-mixed: the hardware
   // approximations (log2, square root and reciprocal square root to about
   // 1 ulp; sin and cos of 2 pi u with u in turns), whose errors enter only
@@ -529,22 +535,22 @@ AVM_FN void azimuth(const TV&, float u, float* sp, float* cp) { M<float>::sincos
 // Direction of (dx, dy, dz) turned by polar angle theta (cos_t) and azimuth
 // phi = 2 pi u_phi.  The transverse length s = sqrt(dx^2 + dy^2) avoids the
 // cancellation of sqrt(1 - dz^2) next to the poles, so |d'| = 1 to rounding.
-template <class R, class TV>
-AVM_FN void turn(const TV& T, R dx, R dy, R dz, R cos_t, R u_phi, R& ox, R& oy, R& oz) {
+// sp, cp: sin and cos of phi.
+template <class R>
+AVM_FN void turn(R sp, R cp, R dx, R dy, R dz, R cos_t, R& ox, R& oy, R& oz) {
   const R st2 = M<R>::fma(-cos_t, cos_t, R(1));
-  const R sin_t = st2 > R(0) ? M<R>::sqrt_s(st2) : R(0);
-  R sp, cp;
-  azimuth(T, u_phi, &sp, &cp);
+  const R sin_t = M<R>::sqrt_0(st2);
   const R q = M<R>::fma(dx, dx, dy * dy);
   const R tiny = sizeof(R) == 8 ? R(1e-24) : R(1e-12);
-  if (q > tiny) {
-    const R inv_s = M<R>::rsqrt_s(q);
-    const R s = q * inv_s;
-    const R a = sin_t * inv_s;
-    ox = M<R>::fma(dx, cos_t, a * M<R>::fma(dx * dz, cp, -dy * sp));
-    oy = M<R>::fma(dy, cos_t, a * M<R>::fma(dy * dz, cp, dx * sp));
-    oz = M<R>::fma(dz, cos_t, -s * sin_t * cp);
-  } else {
+  // (the general form is evaluated in any case; its values are not used next
+  // to the poles, where it may not be finite)
+  const R inv_s = M<R>::rsqrt_s(q);
+  const R s = q * inv_s;
+  const R a = sin_t * inv_s;
+  ox = M<R>::fma(dx, cos_t, a * M<R>::fma(dx * dz, cp, -dy * sp));
+  oy = M<R>::fma(dy, cos_t, a * M<R>::fma(dy * dz, cp, dx * sp));
+  oz = M<R>::fma(dz, cos_t, -s * sin_t * cp);
+  if (!(q > tiny)) {
     ox = sin_t * cp;
     oy = sin_t * sp;
     oz = (dz < R(0) ? R(-1) : R(1)) * cos_t;
@@ -578,13 +584,10 @@ AVM_FN int roots2(R A, R B, R C, R& r1, R& r2) {
   return 2;
 }
 
-// First exit time in (0, T] of z(s) = z0 + vz s + az s^2 / 2 from the slab
-// [zlo, zhi): arrival at zhi, or a crossing below zlo with dz/ds < 0 (s = 0
-// counts when sitting on zlo moving down).  A cheap bound on the extremes of
-// the parabola over [0, T] rules out the common no-exit case before any root
-// is taken.  FP64 in both precisions.
-AVM_FN uint32_t slab_exit(double z0, double vz, double az, double zlo, double zhi, double T,
-                          double& s_exit) {
+// Whether the parabola z(s) = z0 + vz s + az s^2 / 2 stays inside [zlo, zhi)
+// over [0, T]: a bound on its extremes, which rules out the common case
+// before any root is taken (false: it may leave).
+AVM_FN bool slab_inside(double z0, double vz, double az, double zlo, double zhi, double T) {
   const double zT = __builtin_fma(0.5 * az * T, T, __builtin_fma(vz, T, z0));
   // margin: a relative 1e-12 of the coordinates keeps the filter conservative
   const double m = 1e-12 * (fabs(z0) + fabs(zhi) + fabs(zlo) + fabs(vz * T) + fabs(az * T * T));
@@ -596,7 +599,15 @@ AVM_FN uint32_t slab_exit(double z0, double vz, double az, double zlo, double zh
   // by 2 az, without a division
   if (inside && vz * az < 0.0 && fabs(vz) < fabs(az) * T)
     inside = 2.0 * az * (z0 - (az > 0.0 ? lo : hi)) > vz * vz;
-  if (inside) return 0;
+  return inside;
+}
+
+// First exit time in (0, T] of z(s) = z0 + vz s + az s^2 / 2 from the slab
+// [zlo, zhi): arrival at zhi, or a crossing below zlo with dz/ds < 0 (s = 0
+// counts when sitting on zlo moving down).  FP64 in both precisions.
+AVM_FN uint32_t slab_exit(double z0, double vz, double az, double zlo, double zhi, double T,
+                          double& s_exit) {
+  if (slab_inside(z0, vz, az, zlo, zhi, T)) return 0;
   double best = __builtin_inf();
   uint32_t side = 0;
   double r1 = 0.0, r2 = 0.0;
@@ -685,7 +696,7 @@ struct Elec {
   // on advances k, so k = n_null + n_masked + n_band + n_real - [attached])
   uint32_t n_real, n_ion, n_masked, n_band, n_over;
   uint32_t trace;  // decision trace (trace_step)
-  R Ex, Ey, Ez;  // slab: the avalanche's field, loaded once per electron
+  R ax, ay, az;  // slab: acceleration in the avalanche's field, formed once per electron
   // induced signal: weighting potential where the current bin piece began,
   // time and index of the next bin edge
   double sphi, snext;
@@ -696,12 +707,13 @@ template <class R>
 struct Child {
   R vx, vy, vz, e;
   uint64_t eid;
-  R pen;      // pending ionisation: energy at the collision; pending
-              // boundary exit: the flight's end time (STEP_EXIT)
+  R pen;      // pending ionisation: energy at the collision; pending end
+              // of the electron: the flight's duration (STEP_EXIT)
   int32_t pc; // pending ionisation: channel
 };
 
-enum : int32_t { STEP_CONTINUE = 0, STEP_IONISED = 1, STEP_DONE = 2, STEP_EXIT = 3 };
+// (STEP_DONE carries the termination status: STEP_DONE + status)
+enum : int32_t { STEP_NONE = -1, STEP_CONTINUE = 0, STEP_IONISED = 1, STEP_EXIT = 2, STEP_DONE = 16 };
 
 // Decision trace of an electron: a running 32-bit hash over its real
 // collisions, masked nulls and band cuts in flight order, so that two runs
@@ -751,14 +763,21 @@ template <> struct Sel<float> {
   AVM_FN static float inv_2ka(const RunParams& P) { return P.inv_2ka_f; }
 };
 
+// A collision with channel 0 needs no look at its window or kind.
+template <class C>
+AVM_FN bool channel0_elastic(const C& ch) {
+  return ch.kind == CH_ELASTIC && ch.e_lo <= 0.0 && ch.e_hi == __builtin_inf();
+}
+
 // The global-memory tables of precision R (no LDS copies).
 template <class R> AVM_FN TabView<R> global_view(const GasDev& G);
 template <> AVM_FN TabView<double> global_view<double>(const GasDev& G) {
-  return TabView<double>{G.total, G.cum0, G.n_bins + 1, G.band_gamma, G.band_inv, G.band_edge, G.ch, G.sct};
+  return TabView<double>{G.total,      G.cum0,     G.x_top,     channel0_elastic(G.ch[0]),
+                         G.band_gamma, G.band_inv, G.band_edge, G.ch, G.sct};
 }
 template <> AVM_FN TabView<float> global_view<float>(const GasDev& G) {
-  return TabView<float>{G.total_f, G.cum0_f, G.n_bins + 1, G.band_gamma_f, G.band_inv_f,
-                        G.band_edge_f, G.ch_f, G.sct};
+  return TabView<float>{G.total_f,      G.cum0_f,     G.x_top_f,     channel0_elastic(G.ch_f[0]),
+                        G.band_gamma_f, G.band_inv_f, G.band_edge_f, G.ch_f, G.sct};
 }
 
 // Band tables and channel parameters through either view.  Beyond the LDS
@@ -798,6 +817,7 @@ AVM_FN R band_edge(const GasDev&, const TabFit<R>& T, int32_t b) { return T.bedg
 template <class R>
 AVM_FN ChanP<R> chan(const GasDev&, const TabFit<R>& T, int32_t c) { return T.ch[c]; }
 
+// Band of energy e (a NaN counts as the last band).
 template <class R, class TV>
 AVM_FN int32_t band_of(const GasDev& G, const TV& T, R e) {
   const int32_t nb = G.n_bands;
@@ -847,6 +867,36 @@ AVM_FN int32_t band_of_tabs(const GasDev& G, const TV& T, R e, R& gam, R& inv, R
   return b;
 }
 
+// The same for staged tables.  At most 512 bands: the first guess is off by
+// one at most (rounding at an edge), so one correction settles it, without a
+// branch.  (A guess is below n_bands also for an infinite or NaN energy.)
+template <class R>
+AVM_FN int32_t band_guess(const GasDev& G, R e) {
+  const R x = e * Sel<R>::band_scale(G), top = (R)(G.n_bands - 1);
+  return (int32_t)(uint32_t)(x < top ? x : top);
+}
+template <class R>
+AVM_FN int32_t band_of(const GasDev& G, const TabFit<R>& T, R e) {
+  const int32_t b = band_guess<R>(G, e);
+  const R lo = T.bedge[b - 1], hi = T.bedge[b];
+  return b + (e >= hi ? 1 : 0) - (e < lo ? 1 : 0);
+}
+template <class R>
+AVM_FN int32_t band_of_tabs(const GasDev& G, const TabFit<R>& T, R e, R& gam, R& inv, R& edge) {
+  const int32_t b = band_guess<R>(G, e);
+  const R lo = T.bedge[b - 1], hi = T.bedge[b];
+  gam = T.bgam[b];
+  inv = T.binv[b];
+  edge = hi;
+  const int32_t c = b + (e >= hi ? 1 : 0) - (e < lo ? 1 : 0);
+  if (c != b) {
+    gam = T.bgam[c];
+    inv = T.binv[c];
+    edge = T.bedge[c];
+  }
+  return c;
+}
+
 // Termination status of a position outside the drift region, 0 inside
 // (the geometry is the kernel's kField, the same as F.kind).
 template <class R, int kField>
@@ -862,23 +912,50 @@ AVM_FN uint32_t region_status(const FieldDev& F, const Elec<R>& e) {
   return 0;
 }
 
+// The avalanche's field vector in a slab.
+template <class R>
+AVM_FN void slab_vector(const FieldDev& F, uint32_t aval, R& Ex, R& Ey, R& Ez) {
+  const double* E = F.E + 3 * (size_t)(F.n_E == 1 ? 0u : aval);
+  Ex = (R)E[0];
+  Ey = (R)E[1];
+  Ez = (R)E[2];
+}
+
 // Free flight of duration s from (r, v) with the field frozen at E: the
 // displacement is formed in R and added to the FP64 position.  kMayHaveB =
-// false compiles the B = 0 case only (the banded majorant requires B = 0).
+// false compiles the B = 0 case only (the banded majorant in a slab requires
+// B = 0); propagate_r: the position with B = 0, propagate_b: with B.
+template <class R>
+AVM_FN void propagate_r(const Elec<R>& e, R ax, R ay, R az, R s, double& rx, double& ry, double& rz) {
+  using Mr = M<R>;
+  const R hs2 = R(0.5) * s * s;
+  rx = e.x + (double)Mr::fma(ax, hs2, e.vx * s);
+  ry = e.y + (double)Mr::fma(ay, hs2, e.vy * s);
+  rz = e.z + (double)Mr::fma(az, hs2, e.vz * s);
+}
+
+template <class R>
+AVM_FN void propagate_b(const FieldDev& F, const Elec<R>& e, R ax, R ay, R az, R Ex, R Ey, R Ez, R s,
+                        double& rx, double& ry, double& rz, R& ux, R& uy, R& uz);
+
 template <class R, bool kMayHaveB = true>
 AVM_FN void propagate(const FieldDev& F, const Elec<R>& e, R ax, R ay, R az, R Ex, R Ey, R Ez, R s,
                       double& rx, double& ry, double& rz, R& ux, R& uy, R& uz) {
   using Mr = M<R>;
   if (!kMayHaveB || !F.has_b) {
-    const R hs2 = R(0.5) * s * s;
-    rx = e.x + (double)Mr::fma(ax, hs2, e.vx * s);
-    ry = e.y + (double)Mr::fma(ay, hs2, e.vy * s);
-    rz = e.z + (double)Mr::fma(az, hs2, e.vz * s);
+    propagate_r<R>(e, ax, ay, az, s, rx, ry, rz);
     ux = Mr::fma(ax, s, e.vx);
     uy = Mr::fma(ay, s, e.vy);
     uz = Mr::fma(az, s, e.vz);
-    return;
+  } else {
+    propagate_b<R>(F, e, ax, ay, az, Ex, Ey, Ez, s, rx, ry, rz, ux, uy, uz);
   }
+}
+
+template <class R>
+AVM_FN void propagate_b(const FieldDev& F, const Elec<R>& e, R ax, R ay, R az, R Ex, R Ey, R Ez, R s,
+                        double& rx, double& ry, double& rz, R& ux, R& uy, R& uz) {
+  using Mr = M<R>;
   // constant E and B: uniform acceleration along B, E x B drift plus
   // gyration across it
   const R bx = (R)F.bh[0], by = (R)F.bh[1], bz = (R)F.bh[2];
@@ -1060,378 +1137,149 @@ AVM_FN R band_crossing(const RunParams& P, const Elec<R>& e, R ax, R ay, R az, R
 }
 
 // New velocity after a real collision: the old direction turned by
-// (cos_t, phi = 2 pi uB), speed from the new energy.  (The caller advances
-// the flight index.)
-template <class R, class TV>
-AVM_FN void scatter_to(Elec<R>& e, const RunParams& P, const TV& T, R cos_t, R uB, R e_new) {
+// cos_t and the azimuth phi (its sine sp and cosine cp), speed from the new
+// energy.  (The caller advances the flight index.)
+template <class R>
+AVM_FN void scatter_to(Elec<R>& e, const RunParams& P, R sp, R cp, R cos_t, R e_new) {
   const R v2 = dot3<R>(e.vx, e.vy, e.vz, e.vx, e.vy, e.vz);
-  R dx = R(0), dy = R(0), dz = R(1);
-  if (v2 > R(0)) {
-    const R inv = M<R>::rsqrt_s(v2);
-    dx = e.vx * inv;
-    dy = e.vy * inv;
-    dz = e.vz * inv;
+  const R inv = M<R>::rsqrt_s(v2);
+  R dx = e.vx * inv, dy = e.vy * inv, dz = e.vz * inv;
+  if (!(v2 > R(0))) {  // at rest
+    dx = R(0);
+    dy = R(0);
+    dz = R(1);
   }
   R ox, oy, oz;
-  turn<R>(T, dx, dy, dz, cos_t, uB, ox, oy, oz);
+  turn<R>(sp, cp, dx, dy, dz, cos_t, ox, oy, oz);
   const R sp1 = M<R>::sqrt_s(Sel<R>::two_ka(P) * e_new);
   e.vx = sp1 * ox;
   e.vy = sp1 * oy;
   e.vz = sp1 * oz;
 }
 
-// Collision decision at energy en with selection value r_sel: -1 null,
-// -2 - c masked null (the chosen channel c's window excludes en), otherwise
-// the channel: the smallest c with r_sel < interpolated cumulative rate c
-// (channel 0 first -- the elastic channel dominates -- then a binary search
-// over the rest; interpolated cumulative rates are non-decreasing in c).
-// `close` tells whether r_sel lies within a relative 2^-18 of a rate it was
-// compared with, or en within a relative 2^-18 of the window edge it was
-// compared with (tested by multiplying with the power of two, which is
-// exact, instead of dividing); `over` tells whether en lies above the table.
-constexpr double kCloseRel = 3.814697265625e-6;  // 2^-18
-template <class R, class TV>
-AVM_FN int decide(const GasDev& G, const TV& T, R en, R r_sel, bool& close, bool& over) {
+// The smallest channel c >= 1 with r_sel < interpolated cumulative rate c
+// (a binary search: the interpolated rates are non-decreasing in c); mg takes
+// the smallest distance of r_sel to a rate it was compared with.
+template <class R>
+AVM_FN int search_channel(const GasDev& G, int32_t kb, R f, R g1, bool over, R r_sel, R& mg) {
   using Mr = M<R>;
-  const R x = en * Sel<R>::scale(G);
-  int32_t kb;
-  R f;
+  const int nc = G.n_ch;
+  const R* row0 = Sel<R>::cum(G) + (size_t)kb * nc;
+  const R* row1 = over ? row0 : row0 + nc;
+  int lo = 1, hi = nc - 1;  // answer in [lo, hi]
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    const R cm = over ? row0[mid] : lerp<R>(row0[mid], row1[mid], g1, f);
+    const R dm = Mr::abs_(r_sel - cm);
+    mg = dm < mg ? dm : mg;
+    if (r_sel < cm)
+      hi = mid;
+    else
+      lo = mid + 1;
+  }
+  return lo;
+}
+
+// Total rate and cumulative rate of channel 0 at x bins, from the global
+// tables (above the table: the last node's).
+template <class R>
+AVM_FN void rates_global(const GasDev& G, R x, bool& over, int32_t& kb, R& f, R& nu_tot, R& c0) {
   over = !(x < Sel<R>::x_top(G));
   if (over) {
     kb = G.n_bins;
     f = R(0);
   } else {
-    const R fl = Mr::floor_(x);
+    const R fl = M<R>::floor_(x);
     kb = (int32_t)fl;
     f = x - fl;
   }
   const R g1 = R(1) - f;
-  const bool in_lo = kb + 1 < T.n_lo;  // both nodes in the fast copy
   const R* tot = Sel<R>::total(G);
   const R* cz = Sel<R>::cum0(G);
-  R nu_tot, c0;
-  if (in_lo) {
-    nu_tot = lerp<R>(T.tot[kb], T.tot[kb + 1], g1, f);
-    c0 = lerp<R>(T.cum0[kb], T.cum0[kb + 1], g1, f);
-  } else {
-    nu_tot = over ? tot[kb] : lerp<R>(tot[kb], tot[kb + 1], g1, f);
-    c0 = over ? cz[kb] : lerp<R>(cz[kb], cz[kb + 1], g1, f);
-  }
-  R mg = Mr::abs_(r_sel - nu_tot);
-  if (r_sel >= nu_tot) {
-    close = mg <= R(kCloseRel) * r_sel;
-    return -1;
-  }
+  nu_tot = over ? tot[kb] : lerp<R>(tot[kb], tot[kb + 1], g1, f);
+  c0 = over ? cz[kb] : lerp<R>(cz[kb], cz[kb + 1], g1, f);
+}
+
+// The collision decision: with the interpolated rates at energy en and the
+// selection value r_sel, -1 is a null collision (r_sel >= total rate), -2 - c
+// a masked null (the chosen channel c's window excludes en), otherwise the
+// channel: the smallest c with r_sel < cumulative rate c.  Channel 0 is tried
+// first (the elastic channel dominates); flight_step takes it without
+// reading the window when channel 0 has none.
+//
+// FP32-mixed: a decision is close when r_sel lies within a relative 2^-18 of
+// a rate it was compared with, or en within a relative 2^-18 of the edge of
+// the chosen channel's window (tested by multiplying with the power of two,
+// which is exact, instead of dividing), and is then taken again in FP64.
+constexpr double kCloseRel = 3.814697265625e-6;  // 2^-18
+
+// c or -2 - c by channel c's window; window_close as above.
+AVM_FN int in_window(double e_lo, double e_hi, double ed, int c, bool& window_close) {
+  const double dl = fabs(ed - e_lo), dh = fabs(ed - e_hi);
+  const double d = dl < dh ? dl : dh;
+  window_close = d <= kCloseRel * (ed > 1e-30 ? ed : 1e-30);
+  return ed < e_lo || ed >= e_hi ? -2 - c : c;
+}
+
+// The decision in FP64 from the global tables (close FP32 decisions).
+AVM_FN int decide_64(const GasDev& G, double en, double r_sel, bool& over) {
+  int32_t kb;
+  double f, nu_tot, c0, mg = 0.0;
+  rates_global<double>(G, en * G.scale, over, kb, f, nu_tot, c0);
+  if (r_sel >= nu_tot) return -1;
   int c = 0;
-  R dm = Mr::abs_(r_sel - c0);
-  mg = dm < mg ? dm : mg;
-  if (!(r_sel < c0)) {
-    const int nc = G.n_ch;
-    const R* row0 = Sel<R>::cum(G) + (size_t)kb * nc;
-    const R* row1 = over ? row0 : row0 + nc;
-    int lo = 1, hi = nc - 1;  // answer in [lo, hi]
-#if AVM_SEARCH_WAYS == 4
-    // four-way steps while the range is wide: three probes per step, their
-    // gathers issued together (fewer dependent round trips to L2)
-    while (hi - lo >= 4) {
-      const int p1 = lo + ((hi - lo) >> 2), p2 = lo + ((hi - lo) >> 1), p3 = lo + (3 * (hi - lo) >> 2);
-      const R a1 = row0[p1], a2 = row0[p2], a3 = row0[p3];
-      const R b1 = row1[p1], b2 = row1[p2], b3 = row1[p3];
-      const R c1 = over ? a1 : lerp<R>(a1, b1, g1, f);
-      const R c2 = over ? a2 : lerp<R>(a2, b2, g1, f);
-      const R c3 = over ? a3 : lerp<R>(a3, b3, g1, f);
-      const R d1 = Mr::abs_(r_sel - c1), d2 = Mr::abs_(r_sel - c2), d3 = Mr::abs_(r_sel - c3);
-      mg = d1 < mg ? d1 : mg;
-      mg = d2 < mg ? d2 : mg;
-      mg = d3 < mg ? d3 : mg;
-      if (r_sel < c1) {
-        hi = p1;
-      } else if (r_sel < c2) {
-        lo = p1 + 1;
-        hi = p2;
-      } else if (r_sel < c3) {
-        lo = p2 + 1;
-        hi = p3;
-      } else {
-        lo = p3 + 1;
-      }
-    }
-#endif
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      const R cm = over ? row0[mid] : lerp<R>(row0[mid], row1[mid], g1, f);
-      dm = Mr::abs_(r_sel - cm);
-      mg = dm < mg ? dm : mg;
-      if (r_sel < cm)
-        hi = mid;
-      else
-        lo = mid + 1;
-    }
-    c = lo;
-  }
-  close = mg <= R(kCloseRel) * r_sel;
-  const ChanP<R> cw = chan(G, T, c);
-  const double e_lo = cw.e_lo;
-  const double e_hi = cw.e_hi;
-  const double ed = (double)en;
-  if (sizeof(R) == 4) {
-    const double dl = fabs(ed - e_lo), dh = fabs(ed - e_hi);
-    const double d = dl < dh ? dl : dh;
-    close = close || d <= kCloseRel * (ed > 1e-30 ? ed : 1e-30);
-  }
-  if (ed < e_lo || ed >= e_hi) return -2 - c;
-  return c;
+  if (!(r_sel < c0)) c = search_channel<double>(G, kb, f, 1.0 - f, over, r_sel, mg);
+  bool wc;
+  return in_window(G.ch[c].e_lo, G.ch[c].e_hi, en, c, wc);
 }
 
-// One pass of the loop for electron `e`.  Returns STEP_DONE with `status`
-// set when the electron terminates, STEP_IONISED (with the channel and
-// energy in `child`) when the collision is an ionisation -- the caller then
-// finishes it with complete_ionisation() before the next pass -- otherwise
-// STEP_CONTINUE.
-template <class R, bool kBanded, int kField, bool kSignal = false, class TV>
-AVM_FN int32_t flight_step(Elec<R>& e, const GasDev& G, const TV& T, const FieldDev& F,
-                           const RunParams& P, Child<R>& child, uint32_t& status,
-                           const SignalDev* Q = nullptr) {
-  using Mr = M<R>;
-  constexpr bool kMixed = sizeof(R) == 4;
-  // still inside the volume, with flights and time left?
-  uint32_t st0 = region_status<R, kField>(F, e);
-  st0 = st0 ? st0 : (e.k >= P.k_max ? (uint32_t)ST_ABANDONED : (e.t >= P.t_max ? (uint32_t)ST_TIME : 0u));
-  if (st0) {
-    status = st0;
-    return STEP_DONE;
+// ---- where a flight's random numbers come from ----
+// They depend only on the electron's id and the flight index, not on its
+// state: nlog = -ln u1 and u2 of block 0, uA and the sine and cosine of the
+// azimuth 2 pi uB of block 1.  Every source runs the same functions on the
+// same words, so a flight has the same bits from any of them.
+//
+// RandInline: the lane draws each block where the flight needs it.
+template <class R>
+struct RandInline {
+  AVM_FN void flight(const RunParams& P, uint32_t aval, uint64_t eid, uint32_t k, R& nlog, R& u2) const {
+    const Block w = draw(P, aval, eid, k, 0);
+    nlog = -M<R>::log_s(M<R>::uni(w.w0, w.w1));
+    u2 = M<R>::uni(w.w2, w.w3);
   }
-  const Block w = draw(P, e.aval, e.eid, e.k, 0);
-  const R u1 = Mr::uni(w.w0, w.w1);
-  const R u2 = Mr::uni(w.w2, w.w3);
-  R Ex = e.Ex, Ey = e.Ey, Ez = e.Ez;
-  if (kField == FIELD_POLAR) {
-    polar_field<R>(F, e.x, e.y, Ex, Ey);
-    Ez = R(0);
+  // u2 with 53 bits (FP32-mixed: a decision taken again in FP64)
+  AVM_FN double u2_64(const RunParams& P, uint32_t aval, uint64_t eid, uint32_t k) const {
+    const Block w = draw(P, aval, eid, k, 0);
+    return u53(w.w2, w.w3);
   }
-  const R ka = Sel<R>::k_a(P);
-  const R ax = -ka * Ex, ay = -ka * Ey, az = -ka * Ez;
-  // banded with B (polar-map geometry): raise the band until the helical
-  // energy bound at the flight start lies below its edge
-  constexpr bool kMayHaveB = !kBanded || kField == FIELD_POLAR;
-  const bool helical = kBanded && kMayHaveB && F.has_b;
-  HelixBound hb{};
-  if (helical)
-    hb = helix_bound(F, P, (double)e.vx, (double)e.vy, (double)e.vz, (double)Ex, (double)Ey, (double)Ez);
-  // the current band's tables are read first, and the logarithm (which does
-  // not depend on the band) is formed while they arrive
-  const int32_t band0 = e.band;
-  const R gam0 = kBanded ? band_gamma(G, T, band0) : Sel<R>::gamma(G);
-  const R inv0 = kBanded ? band_inv(G, T, band0) : Sel<R>::inv_gamma(G);
-  const R edge0 = kBanded ? band_edge(G, T, band0) : R(0);
-  const R nlog = -Mr::log_s(u1);
-  // the flight's band: its majorant, inverse and upper edge
-  R gam = gam0, inv_gam = inv0, edge = edge0;
-  if (kBanded && P.look > 0.0 && e.band < G.n_bands - 1) {
-    // lookahead: raise the band to the band of the energy after `look` mean
-    // free times of the current band (the flight energy, or its helical
-    // bound); the choice uses only the state at the flight start
-    const double s_look = P.look * (double)inv0;
-    R e_look;
-    if (helical) {
-      const double vpar = hb.vp + hb.ap * s_look;
-      const double lin = hb.p + hb.q * s_look;
-      const double vperp = lin < hb.m ? lin : hb.m;
-      e_look = (R)((vpar * vpar + vperp * vperp) * P.inv_2ka);
-    } else {
-      const R sl = (R)s_look;
-      const R fx = Mr::fma(ax, sl, e.vx), fy = Mr::fma(ay, sl, e.vy), fz = Mr::fma(az, sl, e.vz);
-      e_look = dot3<R>(fx, fy, fz, fx, fy, fz) * Sel<R>::inv_2ka(P);
-    }
-    R gl, il, el;
-    const int32_t bl = band_of_tabs<R>(G, T, e_look, gl, il, el);
-    if (bl > e.band) {
-      e.band = bl;
-      gam = gl;
-      inv_gam = il;
-      edge = el;
-    }
+  template <class TV>
+  AVM_FN void collision(const TV& T, const RunParams& P, uint32_t aval, uint64_t eid, uint32_t k, R& uA, R& sn,
+                        R& cs) const {
+    const Block w = draw(P, aval, eid, k, 1);
+    uA = M<R>::uni(w.w0, w.w1);
+    azimuth(T, M<R>::uni(w.w2, w.w3), &sn, &cs);
   }
-  if (helical) {
-    const int32_t b1 = e.band;
-    while (e.band < G.n_bands - 1 && (hb.vp * hb.vp + hb.p * hb.p) * P.inv_2ka >= (double)band_edge(G, T, e.band))
-      e.band += 1;
-    if (e.band != b1) {
-      gam = band_gamma(G, T, e.band);
-      inv_gam = band_inv(G, T, e.band);
-    }
-  }
-  const R tau = nlog * inv_gam;
-  R tau_end = tau;
-  int cut = 0;  // 1: band edge, 2: time limit
-  if (helical) {
-    if (e.band < G.n_bands - 1) {
-      // cut where the energy bound reaches the edge: Gamma_b holds before
-      const double tc = helix_root(hb, P, (double)band_edge(G, T, e.band));
-      if (tc < (double)tau_end) {
-        tau_end = down_to<R>(tc);
-        cut = 1;
-      }
-    }
-  } else if (kBanded && e.band < G.n_bands - 1) {
-    const R fx = Mr::fma(ax, tau, e.vx), fy = Mr::fma(ay, tau, e.vy), fz = Mr::fma(az, tau, e.vz);
-    if (dot3<R>(fx, fy, fz, fx, fy, fz) * Sel<R>::inv_2ka(P) >= edge) {
-      const R tc = band_crossing<R>(P, e, ax, ay, az, edge);
-      if (tc < tau_end) {
-        tau_end = tc;
-        cut = 1;
-      }
-    }
-  }
-  const double t_left = P.t_max - e.t;
-  if (t_left < (double)tau_end) {
-    tau_end = (R)t_left;
-    cut = 2;
-  }
-  // boundary first passage within (0, tau_end]
-  double rx, ry, rz;
-  R ux, uy, uz;
-  double s_exit = (double)tau_end;
-  uint32_t side = 0;
-  if (kField == FIELD_SLAB) {
-    side = slab_exit(e.z, (double)e.vz, (double)az, F.z_lo, F.z_hi, (double)tau_end, s_exit);
-    propagate<R, kMayHaveB>(F, e, ax, ay, az, Ex, Ey, Ez, side ? (R)s_exit : tau_end, rx, ry, rz, ux, uy, uz);
-    if (side) rz = side == ST_HIGH ? F.z_hi : F.z_lo;
-  } else {
-    propagate<R, kMayHaveB>(F, e, ax, ay, az, Ex, Ey, Ez, tau_end, rx, ry, rz, ux, uy, uz);
-    const double r2 = rx * rx + ry * ry;
-    if (r2 <= F.a2 || r2 >= F.b2) {
-      // the flight ends on the wire or beyond the tube: the electron stops
-      // here, unchanged, and the caller finds the crossing with
-      // finish_exit() after the pass, for all such lanes of the wave at once
-      child.pen = tau_end;
-      return STEP_EXIT;
-    }
-  }
-  if (kSignal) signal_flight<R, kMayHaveB, kField>(*Q, F, e, ax, ay, az, Ex, Ey, Ez,
-                                                   e.t + (side ? s_exit : (double)tau_end));
-  e.x = rx; e.y = ry; e.z = rz;
-  e.vx = ux; e.vy = uy; e.vz = uz;
-  e.t = e.t + (side ? s_exit : (double)tau_end);
-  // the rest runs to a single exit: the outcome is kept in `st` (a
-  // termination status) and `ret`, so the paths share one join
-  uint32_t st = side ? side : (cut == 2 ? (uint32_t)ST_TIME : 0u);
-  int32_t ret = STEP_CONTINUE;
-  if (st == 0) {
-    if (kBanded && cut == 1) {
-      // restart at the band edge with the next majorant; the band index is
-      // advanced explicitly, never re-derived from the rounded energy
-      e.band += 1;
-      e.n_band += 1;
-      e.trace = trace_step(e.trace, e.k, TRACE_BAND);
-    } else {
-      // collision?
-      const R en = dot3<R>(e.vx, e.vy, e.vz, e.vx, e.vy, e.vz) * Sel<R>::inv_2ka(P);
-      if (!(en < Mr::inf())) {
-        st = ST_ERROR;
-      } else {
-        bool close, over;
-        int c = decide<R>(G, T, en, u2 * gam, close, over);
-        if (kMixed && close) {
-          // too close to call in FP32: decide again in FP64 for this state
-          const double vx = (double)e.vx, vy = (double)e.vy, vz = (double)e.vz;
-          const double en64 = dot3<double>(vx, vy, vz, vx, vy, vz) * P.inv_2ka;
-          bool close64;
-          c = decide<double>(G, global_view<double>(G), en64, u53(w.w2, w.w3) * (double)gam, close64, over);
-        }
-        if (over) e.n_over += 1;
-        R e_band = en;  // energy whose band the next flight starts in
-        if (c < 0) {
-          if (c != -1) {
-            e.n_masked += 1;
-            e.trace = trace_step(e.trace, e.k, TRACE_MASKED + (uint32_t)(-2 - c));
-          }
-        } else {
-          e.n_real += 1;
-          e.trace = trace_step(e.trace, e.k, (uint32_t)c);
-          const ChanP<R> ch = chan(G, T, c);
-          const int32_t kind = ch.kind;
-          if (kind == CH_ATTACHMENT) {
-            st = ST_ATTACHED;
-          } else if (kind == CH_IONISATION) {
-            // finished by complete_ionisation() (the caller batches it)
-            child.pen = en;
-            child.pc = c;
-            ret = STEP_IONISED;
-          } else {
-            const Block w1 = draw(P, e.aval, e.eid, e.k, 1);
-            const R uA = Mr::uni(w1.w0, w1.w1);
-            const R uB = Mr::uni(w1.w2, w1.w3);
-            R e_new = en, cos_t = R(1);
-            if (kind == CH_ELASTIC) {
-              const R cchi = ch.angular ? R(1) - R(2) * uA / Mr::fma(R(1) - uA, en * ch.inv_screen8, R(1))
-                                        : R(1) - R(2) * uA;
-              e_new = en * (R(1) - ch.el_loss * (R(1) - cchi));
-              cos_t = (ch.mu + cchi) * Mr::rsqrt_s(Mr::fma(ch.two_mu, cchi, ch.mu2p1));
-            } else {  // excitation
-              if (ch.pen_prob > R(0)) {
-                // Penning transfer, decided by the first uniform of block 2:
-                // the excitation and its transfer electron are finished with
-                // the ionisations after the pass
-                const Block w2 = draw(P, e.aval, e.eid, e.k, 2);
-                if (Mr::uni(w2.w0, w2.w1) < ch.pen_prob) {
-                  child.pen = en;
-                  child.pc = c;
-                  ret = STEP_IONISED;
-                }
-              }
-              e_new = en - ch.loss;
-              cos_t = R(1) - R(2) * uA;
-            }
-            if (ret == STEP_CONTINUE) {
-              scatter_to<R>(e, P, T, cos_t, uB, e_new);
-              e_band = e_new;
-            }
-          }
-        }
-        // one band search for the null and the real-collision paths
-        if (kBanded && st == 0 && ret == STEP_CONTINUE) e.band = band_of<R>(G, T, e_band);
-      }
-    }
-  }
-  // every flight that goes on (null or masked collision, band cut, real
-  // collision) advances the flight index; an ionisation's is advanced when
-  // it is completed (its blocks j = 1..3 belong to this index)
-  if (st == 0 && ret == STEP_CONTINUE) e.k += 1;
-  status = st;
-  return st ? STEP_DONE : ret;
-}
+};
 
-// The flight of a STEP_EXIT (polar-map geometry): the electron stands at
-// the flight start; its flight of duration tau_end (child.pen) ends on the
-// wire or beyond the tube.  Finds the time the boundary is crossed,
-// between the flight start (inside) and its end (outside): a bracket
+// The crossing of a polar-map flight that starts inside and ends, after
+// s_exit, on the wire or beyond the tube (r2: rho^2 there).  Finds the time
+// the boundary is crossed: a bracket
 // [lo, hi] on the inside/outside predicate, shrunk at false-position points
 // of g(s) = R^2 - rho(s)^2 (wire) or rho(s)^2 - R^2 (tube), negative
 // inside, with the Illinois halving of the stale end's value, and at the
 // midpoint when the interpolant leaves the bracket; it stops when the
 // bracket is a few ulps wide (excursions that leave and re-enter within one
-// flight are not detected).  Moves the electron to the crossing (on the
-// boundary surface) and returns its status, ST_WIRE or ST_TUBE.  The lanes
-// of a wave that ended a pass this way search together.
-template <class R, bool kBanded, bool kSignal = false>
-AVM_FN uint32_t finish_exit(Elec<R>& e, const FieldDev& F, const RunParams& P, R tau_end,
-                            const SignalDev* Q = nullptr) {
+// flight are not detected).  Gives the crossing's time, position (on the
+// boundary surface) and velocity, and returns ST_WIRE or ST_TUBE.
+template <class R>
+AVM_FN uint32_t cylinder_exit(const Elec<R>& e, const FieldDev& F, R ax, R ay, R az, R Ex, R Ey, R Ez, double r2,
+                              double& s_exit, double& rx, double& ry, double& rz, R& ux, R& uy, R& uz) {
   constexpr bool kMayHaveB = true;  // polar-map geometry
-  R Ex = e.Ex, Ey = e.Ey, Ez = e.Ez;
-  polar_field<R>(F, e.x, e.y, Ex, Ey);
-  Ez = R(0);
-  const R ka = Sel<R>::k_a(P);
-  const R ax = -ka * Ex, ay = -ka * Ey, az = -ka * Ez;
-  double rx, ry, rz;
-  R ux, uy, uz;
-  propagate<R, kMayHaveB>(F, e, ax, ay, az, Ex, Ey, Ez, tau_end, rx, ry, rz, ux, uy, uz);
-  const double r2 = rx * rx + ry * ry;
   const bool to_wire = r2 <= F.a2;
   const double R2 = to_wire ? F.a2 : F.b2;
   const double sg = to_wire ? -1.0 : 1.0;
   const double q0 = e.x * e.x + e.y * e.y;
-  double lo = 0.0, hi = (double)tau_end;
+  double lo = 0.0, hi = s_exit;
   double glo = sg * (q0 - R2), ghi = sg * (r2 - R2);
   int last = 0;
   // a few ulps of the flight time in the step's precision (the trial
@@ -1457,18 +1305,344 @@ AVM_FN uint32_t finish_exit(Elec<R>& e, const FieldDev& F, const RunParams& P, R
       last = 1;
     }
   }
-  const double s_exit = hi;
+  s_exit = hi;
   propagate<R, kMayHaveB>(F, e, ax, ay, az, Ex, Ey, Ez, (R)s_exit, rx, ry, rz, ux, uy, uz);
   const double q2 = rx * rx + ry * ry;
   const uint32_t side = q2 <= F.a2 ? ST_WIRE : ST_TUBE;
   const double sc = (side == ST_WIRE ? F.a : F.b) / sqrt(q2);
   rx = rx * sc;
   ry = ry * sc;
-  if (kSignal) signal_flight<R, kMayHaveB, FIELD_POLAR>(*Q, F, e, ax, ay, az, Ex, Ey, Ez, e.t + s_exit);
+  return side;
+}
+
+// Whether a flight from z0 to z1 whose linear part is w = vz s stays inside
+// the slab: no point of its parabola is further from the segment [z0, z1]
+// than |w| / 2 from z0 (an interior vertex lies w^2 / (4 |h|) from z0, with h
+// the quadratic part, and |w| < 2 |h| there).  z_half leaves a margin for the
+// rounding of the positions, so a true answer is also slab_inside()'s.
+template <class R>
+AVM_FN bool slab_clear(const FieldDev& F, double z0, double z1, R w) {
+  const double half = sizeof(R) == 8 ? F.z_half : F.z_half_f;
+  return __builtin_fma(0.5, fabs((double)w), fabs(z0 - F.z_mid)) < half && fabs(z1 - F.z_mid) < half;
+}
+
+// One pass of the loop for electron `e`.  Returns STEP_CONTINUE when the
+// electron flies on; STEP_IONISED (with the channel and energy in `child`)
+// when the collision is an ionisation -- the caller then finishes it with
+// complete_ionisation() before the next pass; STEP_EXIT (with the flight's
+// duration in `child`) when the flight may leave the volume or run into the
+// time or flight limit: the electron stands at the flight's start, unchanged,
+// and the caller settles it with finish_exit() after the pass, for all such
+// lanes of the wave at once; STEP_DONE + status when the electron ended in a
+// collision.  `clear`: finish_exit() found that this flight does not end the
+// electron (reset here).
+//
+// What bounds it: in a full wave the VALU instructions of a pass, paid by all
+// lanes for every path that any lane takes; in a nearly empty wave their
+// number too (a lone wave issues one instruction, vector or scalar, every
+// four cycles), so the step is written with few branches: values are
+// selected where that is shorter than a branch, and what ends an electron
+// (once per ~200 flights, but in every third flight of a full wave) is left
+// to finish_exit().  Against a step with the boundary solved in the flight,
+// one branch per outcome and searched bands: 665 -> about 560 vector
+// instructions per flight of a full wave; 8192 avalanches 505 -> 450 ms, one
+// avalanche 7.2 -> 5.7 ms (FP64), 1000 in FP32-mixed 15.5 -> 13.2 ms.
+template <class R, bool kBanded, int kField, bool kSignal = false, class TV, class RS>
+AVM_FN int32_t flight_step(Elec<R>& e, const GasDev& G, const TV& T, const FieldDev& F,
+                           const RunParams& P, Child<R>& child, bool& clear, RS rs,
+                           const SignalDev* Q = nullptr) {
+  using Mr = M<R>;
+  constexpr bool kMixed = sizeof(R) == 4;
+  constexpr bool kMayHaveB = !kBanded || kField == FIELD_POLAR;
+  R Ex = R(0), Ey = R(0), Ez = R(0);
+  R ax = e.ax, ay = e.ay, az = e.az;
+  if (kField == FIELD_POLAR) {
+    polar_field<R>(F, e.x, e.y, Ex, Ey);
+    const R ka = Sel<R>::k_a(P);
+    ax = -ka * Ex;
+    ay = -ka * Ey;
+    az = -ka * Ez;
+  } else if (kMayHaveB && F.has_b) {
+    slab_vector<R>(F, e.aval, Ex, Ey, Ez);
+  }
+  // banded with B (polar-map geometry): raise the band until the helical
+  // energy bound at the flight start lies below its edge
+  const bool helical = kBanded && kMayHaveB && F.has_b;
+  HelixBound hb{};
+  if (helical)
+    hb = helix_bound(F, P, (double)e.vx, (double)e.vy, (double)e.vz, (double)Ex, (double)Ey, (double)Ez);
+  // the current band's tables are read first, and the flight's draws (which
+  // do not depend on the band) are formed while they arrive
+  int32_t band = e.band;
+  // the flight's band: its majorant, inverse and upper edge
+  R gam = kBanded ? band_gamma(G, T, band) : Sel<R>::gamma(G);
+  R inv_gam = kBanded ? band_inv(G, T, band) : Sel<R>::inv_gamma(G);
+  R edge = kBanded ? band_edge(G, T, band) : R(0);
+  R nlog, u2;
+  rs.flight(P, e.aval, e.eid, e.k, nlog, u2);
+  if (kBanded && P.look > 0.0) {
+    // lookahead: raise the band to the band of the energy after `look` mean
+    // free times of the current band (the flight energy, or its helical
+    // bound); the choice uses only the state at the flight start
+    const double s_look = P.look * (double)inv_gam;
+    R e_look;
+    if (helical) {
+      const double vpar = hb.vp + hb.ap * s_look;
+      const double lin = hb.p + hb.q * s_look;
+      const double vperp = lin < hb.m ? lin : hb.m;
+      e_look = (R)((vpar * vpar + vperp * vperp) * P.inv_2ka);
+    } else {
+      const R sl = (R)s_look;
+      const R fx = Mr::fma(ax, sl, e.vx), fy = Mr::fma(ay, sl, e.vy), fz = Mr::fma(az, sl, e.vz);
+      e_look = dot3<R>(fx, fy, fz, fx, fy, fz) * Sel<R>::inv_2ka(P);
+    }
+    R gl, il, el;
+    const int32_t bl = band_of_tabs<R>(G, T, e_look, gl, il, el);
+    const bool up = bl > band;  // (never from the last band)
+    gam = up ? gl : gam;
+    inv_gam = up ? il : inv_gam;
+    edge = up ? el : edge;
+    band = up ? bl : band;
+  }
+  if (helical) {
+    const int32_t b1 = band;
+    while (band < G.n_bands - 1 && (hb.vp * hb.vp + hb.p * hb.p) * P.inv_2ka >= (double)band_edge(G, T, band))
+      band += 1;
+    if (band != b1) {
+      gam = band_gamma(G, T, band);
+      inv_gam = band_inv(G, T, band);
+    }
+  }
+  R tau = nlog * inv_gam;
+  bool cut = false;  // at the band's edge
+  // the flight's end: position r, velocity u, and energy en
+  R ux, uy, uz, en;
+  if (kMayHaveB && F.has_b) {
+    if (helical && band < G.n_bands - 1) {
+      // cut where the energy bound reaches the edge: Gamma_b holds before
+      const double tc = helix_root(hb, P, (double)band_edge(G, T, band));
+      if (tc < (double)tau) {
+        tau = down_to<R>(tc);
+        cut = true;
+      }
+    }
+  } else {
+    ux = Mr::fma(ax, tau, e.vx);
+    uy = Mr::fma(ay, tau, e.vy);
+    uz = Mr::fma(az, tau, e.vz);
+    en = dot3<R>(ux, uy, uz, ux, uy, uz) * Sel<R>::inv_2ka(P);
+    if (kBanded && en >= edge && band < G.n_bands - 1) {
+      const R tc = band_crossing<R>(P, e, ax, ay, az, edge);
+      if (tc < tau) {
+        tau = tc;
+        cut = true;
+        ux = Mr::fma(ax, tau, e.vx);
+        uy = Mr::fma(ay, tau, e.vy);
+        uz = Mr::fma(az, tau, e.vz);
+      }
+    }
+  }
+  double rx, ry, rz;
+  if (kMayHaveB && F.has_b) {
+    propagate_b<R>(F, e, ax, ay, az, Ex, Ey, Ez, tau, rx, ry, rz, ux, uy, uz);
+    en = dot3<R>(ux, uy, uz, ux, uy, uz) * Sel<R>::inv_2ka(P);
+  } else {
+    propagate_r<R>(e, ax, ay, az, tau, rx, ry, rz);
+  }
+  // the flight goes on when it starts and ends inside the volume and before
+  // the time and flight limits
+  const double t_left = P.t_max - e.t;
+  const double q0 = e.x * e.x + e.y * e.y, q1 = rx * rx + ry * ry;
+  bool go = t_left > (double)tau && e.k < P.k_max;
+  if (kField == FIELD_SLAB)
+    go = go && slab_clear<R>(F, e.z, rz, e.vz * tau);
+  else
+    go = go && q0 > F.a2 && q0 < F.b2 && q1 > F.a2 && q1 < F.b2;
+  if (!go) {
+    // near a boundary or a limit: the exact conditions
+    go = !region_status<R, kField>(F, e) && e.k < P.k_max && !(e.t >= P.t_max) && !(t_left < (double)tau);
+    if (kField == FIELD_SLAB)
+      go = go && slab_inside(e.z, (double)e.vz, (double)az, F.z_lo, F.z_hi, (double)tau);
+    else
+      go = go && !(q1 <= F.a2 || q1 >= F.b2);
+    if (clear) go = true;
+    clear = false;
+  }
+  child.pen = tau;
+  int32_t ret = STEP_EXIT;
+  if (go) {
+    ret = STEP_CONTINUE;
+    const double t_e = e.t + (double)tau;
+    if (kSignal) signal_flight<R, kMayHaveB, kField>(*Q, F, e, ax, ay, az, Ex, Ey, Ez, t_e);
+    e.x = rx; e.y = ry; e.z = rz;
+    e.vx = ux; e.vy = uy; e.vz = uz;
+    e.t = t_e;
+    if (kBanded && cut) {
+      // restart at the band edge with the next majorant; the band index is
+      // advanced explicitly, never re-derived from the rounded energy
+      band += 1;
+      e.n_band += 1;
+      e.trace = trace_step(e.trace, e.k, TRACE_BAND);
+    } else {
+      // collision?  Rates from the staged low nodes, else (and for an energy
+      // that is not finite) from the global tables
+      const R x = en * Sel<R>::scale(G);
+      int32_t kb;
+      R f, nu_tot, c0;
+      bool over = false;
+      if (x < T.x_lo) {
+        const R fl = Mr::floor_(x);
+        kb = (int32_t)fl;
+        f = x - fl;
+        const R g1 = R(1) - f;
+        nu_tot = lerp<R>(T.tot[kb], T.tot[kb + 1], g1, f);
+        c0 = lerp<R>(T.cum0[kb], T.cum0[kb + 1], g1, f);
+      } else {
+        rates_global<R>(G, x, over, kb, f, nu_tot, c0);
+        if (!(en < Mr::inf())) {
+          ret = STEP_DONE + ST_ERROR;
+          over = false;
+          nu_tot = R(-1);
+        }
+        if (!kMixed && over) e.n_over += 1;
+      }
+      const R r_sel = u2 * gam;
+      const bool first = r_sel < c0;
+      int c = r_sel < nu_tot ? 0 : -1;
+      R mg = Mr::abs_(r_sel - nu_tot);
+      if (kMixed && c == 0) {
+        const R dm = Mr::abs_(r_sel - c0);
+        mg = dm < mg ? dm : mg;
+      }
+      // a channel other than an elastic channel 0 (FP32-mixed: near zero
+      // energy its window's edge may be close)
+      bool wc = false;
+      if (c == 0 && !(first && T.el0 && (!kMixed || en > R(1e-30)))) {
+        if (!first) c = search_channel<R>(G, kb, f, R(1) - f, over, r_sel, mg);
+        const ChanP<R> cw = chan(G, T, c);
+        c = in_window(cw.e_lo, cw.e_hi, (double)en, c, wc);
+      }
+      if (kMixed) {
+        if (mg <= R(kCloseRel) * r_sel || wc) {
+          // too close to call in FP32: decide again in FP64 for this state
+          const double vx = (double)e.vx, vy = (double)e.vy, vz = (double)e.vz;
+          const double en64 = dot3<double>(vx, vy, vz, vx, vy, vz) * P.inv_2ka;
+          c = decide_64(G, en64, rs.u2_64(P, e.aval, e.eid, e.k) * (double)gam, over);
+        }
+        if (over) e.n_over += 1;
+      }
+      R e_band = en;  // energy whose band the next flight starts in
+      if (c != -1) {
+        bool scatter = true;
+        if (!(c == 0 && T.el0)) {
+          if (c < 0) {
+            e.n_masked += 1;
+            e.trace = trace_step(e.trace, e.k, TRACE_MASKED + (uint32_t)(-2 - c));
+            scatter = false;
+          } else {
+            const ChanP<R> ch = chan(G, T, c);
+            bool pending = ch.kind == CH_IONISATION;
+            if (ch.kind == CH_EXCITATION && ch.pen_prob > R(0)) {
+              // Penning transfer, decided by the first uniform of block 2:
+              // the excitation and its transfer electron are finished with
+              // the ionisations after the pass
+              const Block w2 = draw(P, e.aval, e.eid, e.k, 2);
+              pending = Mr::uni(w2.w0, w2.w1) < ch.pen_prob;
+            }
+            if (pending) {
+              // finished by complete_ionisation() (the caller batches it)
+              child.pen = en;
+              child.pc = c;
+              ret = STEP_IONISED;
+              scatter = false;
+            }
+            if (ch.kind == CH_ATTACHMENT) {
+              ret = STEP_DONE + ST_ATTACHED;
+              scatter = false;
+            }
+          }
+        }
+        if (c >= 0) {
+          e.n_real += 1;
+          e.trace = trace_step(e.trace, e.k, (uint32_t)c);
+        }
+        if (scatter) {
+          // one form for elastic collisions and excitations: an elastic
+          // channel's loss, any other's mass ratio and screening are zero
+          const ChanP<R> ch = chan(G, T, c);
+          R uA, sphi, cphi;
+          rs.collision(T, P, e.aval, e.eid, e.k, uA, sphi, cphi);
+          const R cchi = R(1) - R(2) * uA / Mr::fma(R(1) - uA, en * ch.inv_screen8, R(1));
+          const R e_new = en * (R(1) - ch.el_loss * (R(1) - cchi)) - ch.loss;
+          const R lab = (ch.mu + cchi) * Mr::rsqrt_s(Mr::fma(ch.two_mu, cchi, ch.mu2p1));
+          scatter_to<R>(e, P, sphi, cphi, ch.kind == CH_ELASTIC ? lab : cchi, e_new);
+          e_band = e_new;
+        }
+      }
+      // one band search for the null and the real-collision paths
+      if (kBanded) band = band_of<R>(G, T, e_band);
+    }
+    if (kBanded) e.band = band;
+    // every flight that goes on (null or masked collision, band cut, real
+    // collision) advances the flight index; an ionisation's is advanced when
+    // it is completed (its blocks j = 1..3 belong to this index)
+    e.k += ret == STEP_CONTINUE ? 1u : 0u;
+  }
+  return ret;
+}
+
+// Settles a STEP_EXIT flight of duration tau (child.pen): the electron
+// stands at the flight's start.  Returns its termination status, with the
+// electron moved to where it ends -- outside the volume already, out of
+// flights or out of time: where it stands; on the boundary its flight
+// crosses; or where its time runs out in flight -- or 0 when the flight does
+// not end it (a slab flight that only came near a boundary): the caller then
+// lets it fly with `clear` set.  The lanes of a wave that ended a pass this
+// way come here together: at 1 % of the flights, code of this length inside
+// the flight loop ran in every third flight of a full wave.
+template <class R, bool kBanded, int kField, bool kSignal = false>
+AVM_FN uint32_t finish_exit(Elec<R>& e, const FieldDev& F, const RunParams& P, R tau,
+                            const SignalDev* Q = nullptr) {
+  constexpr bool kMayHaveB = !kBanded || kField == FIELD_POLAR;
+  const uint32_t st0 = region_status<R, kField>(F, e);
+  if (st0) return st0;
+  if (e.k >= P.k_max) return ST_ABANDONED;
+  if (e.t >= P.t_max) return ST_TIME;
+  const double t_left = P.t_max - e.t;
+  const bool late = t_left < (double)tau;
+  if (late) tau = (R)t_left;
+  R Ex = R(0), Ey = R(0), Ez = R(0);
+  R ax = e.ax, ay = e.ay, az = e.az;
+  if (kField == FIELD_POLAR) {
+    polar_field<R>(F, e.x, e.y, Ex, Ey);
+    const R ka = Sel<R>::k_a(P);
+    ax = -ka * Ex;
+    ay = -ka * Ey;
+    az = -ka * Ez;
+  } else if (kMayHaveB && F.has_b) {
+    slab_vector<R>(F, e.aval, Ex, Ey, Ez);
+  }
+  double s_exit = (double)tau;
+  uint32_t side = 0;
+  double rx, ry, rz;
+  R ux, uy, uz;
+  if (kField == FIELD_SLAB) {
+    side = slab_exit(e.z, (double)e.vz, (double)az, F.z_lo, F.z_hi, (double)tau, s_exit);
+    propagate<R, kMayHaveB>(F, e, ax, ay, az, Ex, Ey, Ez, side ? (R)s_exit : tau, rx, ry, rz, ux, uy, uz);
+    if (side) rz = side == ST_HIGH ? F.z_hi : F.z_lo;
+  } else {
+    propagate<R, kMayHaveB>(F, e, ax, ay, az, Ex, Ey, Ez, tau, rx, ry, rz, ux, uy, uz);
+    const double r2 = rx * rx + ry * ry;
+    if (r2 <= F.a2 || r2 >= F.b2)
+      side = cylinder_exit<R>(e, F, ax, ay, az, Ex, Ey, Ez, r2, s_exit, rx, ry, rz, ux, uy, uz);
+  }
+  if (!side && !late) return 0;
+  const double t_e = e.t + s_exit;
+  if (kSignal) signal_flight<R, kMayHaveB, kField>(*Q, F, e, ax, ay, az, Ex, Ey, Ez, t_e);
   e.x = rx; e.y = ry; e.z = rz;
   e.vx = ux; e.vy = uy; e.vz = uz;
-  e.t = e.t + s_exit;
-  return side;
+  e.t = t_e;
+  return side ? side : (uint32_t)ST_TIME;
 }
 
 // Finishes an ionisation (or a Penning transfer) decided by flight_step
@@ -1511,7 +1685,8 @@ AVM_FN void complete_ionisation(Elec<R>& e, const GasDev& G, const TV& T,
   child.e = es;
   child.eid = (((uint64_t)w3.w3 << 32) | (uint64_t)w3.w2) & 0x7FFFFFFFFFFFFFFFull;
   e.n_ion += 1;
-  scatter_to<R>(e, P, T, R(1) - R(2) * uA, uB, e_new);
+  azimuth(T, uB, &sp, &cp);
+  scatter_to<R>(e, P, sp, cp, R(1) - R(2) * uA, e_new);
   e.k += 1;
   if (kBanded) e.band = band_of<R>(G, T, e_new);
 }

@@ -187,11 +187,13 @@ __global__ void k_load_primaries(const PrimaryRec* __restrict__ prim, uint64_t n
 }
 
 template <class R>
-AVM_FN void slab_field(const FieldDev& F, uint32_t aval, Elec<R>& e) {
-  const double* E = F.E + 3 * (size_t)(F.n_E == 1 ? 0u : aval);
-  e.Ex = (R)E[0];
-  e.Ey = (R)E[1];
-  e.Ez = (R)E[2];
+AVM_FN void slab_field(const FieldDev& F, const RunParams& P, Elec<R>& e) {
+  R Ex, Ey, Ez;
+  slab_vector<R>(F, e.aval, Ex, Ey, Ez);
+  const R ka = Sel<R>::k_a(P);
+  e.ax = -ka * Ex;
+  e.ay = -ka * Ey;
+  e.az = -ka * Ez;
 }
 
 // Null collisions of a terminated electron: every flight that went on
@@ -383,8 +385,8 @@ AVM_FN void load_elec_tail(const GasDev& G, const TV& T, const FieldDev& F,
   e.n_real = 0; e.n_ion = 0; e.n_masked = 0; e.n_band = 0; e.n_over = 0;
   e.trace = 0;
   e.band = kBanded ? band_of<R>(G, T, energy<R>(P, e.vx, e.vy, e.vz)) : G.n_bands - 1;
-  e.Ex = R(0); e.Ey = R(0); e.Ez = R(0);
-  if (kField == FIELD_SLAB) slab_field<R>(F, e.aval, e);
+  e.ax = R(0); e.ay = R(0); e.az = R(0);
+  if (kField == FIELD_SLAB) slab_field<R>(F, P, e);
 }
 
 // ---------------------------------------------------------------------------
@@ -425,28 +427,30 @@ __global__ void __launch_bounds__(kBlock) k_generation(GasDev G, FieldDev F, Run
     e.n_real = live.n_real; e.n_ion = live.n_ion;
     e.n_masked = live.n_masked; e.n_band = live.n_band; e.n_over = live.n_overflow;
     e.trace = live.trace;
-    e.Ex = R(0); e.Ey = R(0); e.Ez = R(0);
-    if (kField == FIELD_SLAB) slab_field<R>(F, e.aval, e);
+    e.ax = R(0); e.ay = R(0); e.az = R(0);
+    if (kField == FIELD_SLAB) slab_field<R>(F, P, e);
     uint32_t status = 0;
+    bool clear = false;
     int32_t r;
     const uint64_t t_start = wall_clock64();
     uint32_t n = 0;
     do {
-      r = flight_step<R, kBanded, kField>(e, G, T, F, P, child, status);
-      if (r == STEP_CONTINUE && (++n & 4095u) == 0 && wall_clock64() - t_start > P.budget_ticks) {
-        // out of time: stop this electron, flag the run
-        __hip_atomic_store(&ctr->timeout, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        status = ST_ERROR;
-        r = STEP_DONE;
+      do {
+        r = flight_step<R, kBanded, kField>(e, G, T, F, P, child, clear, RandInline<R>{});
+        if (r == STEP_CONTINUE && (++n & 4095u) == 0 && wall_clock64() - t_start > P.budget_ticks) {
+          // out of time: stop this electron, flag the run
+          __hip_atomic_store(&ctr->timeout, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          r = STEP_DONE + ST_ERROR;
+        }
+      } while (r == STEP_CONTINUE);
+      // the lanes of the wave that may leave the volume are settled together
+      if (r == STEP_EXIT) {
+        status = finish_exit<R, kBanded, kField>(e, F, P, child.pen);
+        clear = status == 0;
       }
-    } while (r == STEP_CONTINUE);
-    if (kField == FIELD_POLAR && r == STEP_EXIT) {
-      // the crossing of the flight that left the volume (the lanes of the
-      // wave that got here search together)
-      status = finish_exit<R, kBanded>(e, F, P, child.pen);
-      r = STEP_DONE;
-    }
-    if (r == STEP_DONE) {
+    } while (clear);
+    if (r >= STEP_DONE) status = (uint32_t)(r - STEP_DONE);
+    if (status) {
       write_end(S, slot, e, P, status);
       term = status;
     } else {
@@ -572,7 +576,7 @@ __global__ void __launch_bounds__(kPBlock)
   // nodes, and the band tables, one copy per block
   constexpr int kLdsNodes = kLdsBytes / (int)sizeof(R);
   __shared__ R s_tot[kLdsNodes], s_cum0[kLdsNodes];
-  __shared__ R s_bg[kLdsBands], s_bi[kLdsBands], s_be[kLdsBands];
+  __shared__ R s_bg[kLdsBands], s_bi[kLdsBands], s_be[kLdsBands + 1];  // (s_be[0]: below band 0)
   __shared__ ChanP<R> s_ch[kLdsChannels];
   __shared__ double s_sct[2 * kAzN];
   __shared__ unsigned long long s_tally[kTally];
@@ -592,19 +596,22 @@ __global__ void __launch_bounds__(kPBlock)
   for (int b = threadIdx.x; b < n_lb; b += kPBlock) {
     s_bg[b] = Tg.bgam[b];
     s_bi[b] = Tg.binv[b];
-    s_be[b] = Tg.bedge[b];
+    // (kFit: the last band has no edge)
+    s_be[b + 1] = kFit && b == G.n_bands - 1 ? (R)__builtin_nan("") : Tg.bedge[b];
   }
+  if (threadIdx.x == 0) s_be[0] = -M<R>::inf();
   const int n_lc = G.n_ch < kLdsChannels ? G.n_ch : kLdsChannels;
   if ((int)threadIdx.x < n_lc) s_ch[threadIdx.x] = Tg.ch[threadIdx.x];
   for (int k = threadIdx.x; k < 2 * kAzN; k += kPBlock) s_sct[k] = G.sct[k];
   __syncthreads();
   using View = std::conditional_t<kFit, TabFit<R>, TabLds<R>>;
-  const View T{(const AVM_LDS R*)s_tot, (const AVM_LDS R*)s_cum0, n_lo, (const AVM_LDS R*)s_bg,
-               (const AVM_LDS R*)s_bi, (const AVM_LDS R*)s_be, (const AVM_LDS ChanP<R>*)s_ch,
-               (const AVM_LDS double*)s_sct};
+  const View T{(const AVM_LDS R*)s_tot, (const AVM_LDS R*)s_cum0, (R)(n_lo - 1), Tg.el0,
+               (const AVM_LDS R*)s_bg, (const AVM_LDS R*)s_bi, (const AVM_LDS R*)s_be + 1,
+               (const AVM_LDS ChanP<R>*)s_ch, (const AVM_LDS double*)s_sct};
   Xfer& X = xfer_all[threadIdx.x >> 6];
   const uint32_t lane = __lane_id();
   bool has = false, cp = false;
+  bool clear = false;  // the lane's next flight does not end its electron (finish_exit)
   unsigned long long n_gone = 0;  // electrons this wave terminated or dropped, not yet in `ended`
   int idle_naps = 0;  // a wave with no electron backs off, longer the longer it stays idle
   unsigned long long claim = kNone;
@@ -620,24 +627,17 @@ __global__ void __launch_bounds__(kPBlock)
     }
     // ---- transport pass
     uint32_t term = 0;  // status of this lane's electron if it terminated in this pass
-    bool xp = false;    // the electron's last flight left the volume (polar map)
-    for (int f = 0; f < flights_per_pass && has && !cp && !xp; ++f) {
-      uint32_t status = 0;
-      const int32_t r = flight_step<R, kBanded, kField, kSignal>(e, G, T, F, P, child, status, &Q);
-      if (r == STEP_IONISED) {
-        cp = true;
-      } else if (r == STEP_DONE) {
-        has = false;
-        term = status;
-      } else if (kField == FIELD_POLAR && r == STEP_EXIT) {
-        xp = true;
-      }
+    int32_t r = has ? STEP_CONTINUE : STEP_NONE;
+    for (int f = 0; f < flights_per_pass && r == STEP_CONTINUE; ++f)
+      r = flight_step<R, kBanded, kField, kSignal>(e, G, T, F, P, child, clear, RandInline<R>{}, &Q);
+    cp = r == STEP_IONISED;
+    // ---- flights of this pass that may end their electron, settled together
+    if (r == STEP_EXIT) {
+      term = finish_exit<R, kBanded, kField, kSignal>(e, F, P, child.pen, &Q);
+      clear = term == 0;
     }
-    // ---- boundary crossings of this pass, found together
-    if (kField == FIELD_POLAR && xp) {
-      term = finish_exit<R, kBanded, kSignal>(e, F, P, child.pen, &Q);
-      has = false;
-    }
+    if (r >= STEP_DONE) term = (uint32_t)(r - STEP_DONE);
+    has = has && term == 0;
     // ---- endpoints of this pass, written together (the state of a
     // terminated electron stays in place until the exchange)
     if (term) {
@@ -713,7 +713,6 @@ __global__ void __launch_bounds__(kPBlock)
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    cp = false;
     // 5. still-idle lanes claim queue entries while the queue has some
     const bool want = !has && claim == kNone && !take;
     const uint64_t m_want = __ballot(want);
