@@ -74,6 +74,7 @@ struct Counters {
   alignas(256) unsigned long long qhead;  // batched: queue entries claimed by lanes
   alignas(256) unsigned long long qtail;  // batched: queue entries published or being published
   alignas(256) unsigned long long ended;  // batched: electrons terminated or dropped, as flushed by waves
+  alignas(256) unsigned long long busy;   // batched: waves that carry electrons
   alignas(256) unsigned long long next;   // plain: size of the next active list
   unsigned long long err;                 // bad primary avalanche id
   unsigned long long timeout;             // a transport kernel ran out of its time budget

@@ -132,6 +132,7 @@ __global__ void k_reset(Counters* ctr, uint64_t n_prim, AvalStats* stats, uint32
     ctr->qhead = 0;
     ctr->qtail = n_prim;
     ctr->ended = 0;
+    ctr->busy = 0;
     ctr->next = 0;
     ctr->err = 0;
     ctr->timeout = 0;
@@ -516,21 +517,103 @@ struct Xfer {
   uint32_t slot[64], aval[64];
 };
 
-// Back-off of a wave with no electron: repeated s_sleep(AVM_IDLE_NAP)
-// (64 cycles each per unit), up to AVM_IDLE_MAX_NAPS in a row (16 x 63:
-// up to ~27 us; measured 8-12 % faster than one short nap on the
-// 1000-avalanche benchmark, where most waves are idle while the avalanches
-// start and end).
-// Waves carrying electrons issue ahead of waves that only poll the queue.
+// Random numbers of the flights ahead, drawn by all lanes of a wave that
+// carries few electrons: lane l draws flight (l mod G) of the (l / G)-th
+// electron, G = 64 / (electrons rounded up to a power of two), so one pass
+// over the two Philox blocks, the logarithm and the azimuth serves G flights
+// of every electron.  They wait in the wave's transfer buffer, which only
+// the exchange uses otherwise (five of its columns).  `ahead` is uniform in
+// the wave; without it the lane draws where the flight needs the block.
+template <class R>
+struct RandWave {
+  const AVM_LDS Xfer* X;
+  uint32_t i;  // entry of the flight
+  bool ahead;
+  AVM_FN void flight(const RunParams& P, uint32_t aval, uint64_t eid, uint32_t k, R& nlog, R& u2) const {
+    if (ahead) {
+      nlog = ((const AVM_LDS R*)X->x)[i];
+      u2 = ((const AVM_LDS R*)X->y)[i];
+    } else {
+      RandInline<R>{}.flight(P, aval, eid, k, nlog, u2);
+    }
+  }
+  AVM_FN double u2_64(const RunParams& P, uint32_t aval, uint64_t eid, uint32_t k) const {
+    return RandInline<R>{}.u2_64(P, aval, eid, k);
+  }
+  template <class TV>
+  AVM_FN void collision(const TV& T, const RunParams& P, uint32_t aval, uint64_t eid, uint32_t k, R& uA, R& sn,
+                        R& cs) const {
+    if (ahead) {
+      uA = ((const AVM_LDS R*)X->z)[i];
+      sn = ((const AVM_LDS R*)X->t)[i];
+      cs = ((const AVM_LDS R*)X->vx)[i];
+    } else {
+      RandInline<R>{}.collision(T, P, aval, eid, k, uA, sn, cs);
+    }
+  }
+};
+
+AVM_FN void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Draws the flights ahead of the lanes with `live` (m = their ballot, not
+// empty); called by every lane of the wave.  Returns log2 of the number of
+// flights drawn per electron; the flights of the electron of rank r start at
+// entry r << that.
+template <class R, class TV>
+AVM_FN uint32_t draw_ahead(AVM_LDS Xfer* X, bool live, uint64_t m, uint32_t rank, const Elec<R>& e,
+                           const RunParams& P, const TV& T) {
+  const uint32_t n = __popcll(m);
+  const uint32_t sh = n > 1 ? (uint32_t)__builtin_clz(n - 1) - 26u : 6u;
+  if (live) {
+    X->aval[rank] = e.aval;
+    X->eid[rank] = e.eid;
+    X->slot[rank] = e.k;
+  }
+  wave_fence();
+  const uint32_t lane = __lane_id();
+  const uint32_t r = lane >> sh;
+  if (r < n) {
+    const uint32_t aval = X->aval[r], k = X->slot[r] + (lane & ((1u << sh) - 1u));
+    const uint64_t eid = X->eid[r];
+    const RandInline<R> own;
+    R a, b, c;
+    own.flight(P, aval, eid, k, a, b);
+    ((AVM_LDS R*)X->x)[lane] = a;
+    ((AVM_LDS R*)X->y)[lane] = b;
+    own.collision(T, P, aval, eid, k, a, b, c);
+    ((AVM_LDS R*)X->z)[lane] = a;
+    ((AVM_LDS R*)X->t)[lane] = b;
+    ((AVM_LDS R*)X->vx)[lane] = c;
+  }
+  wave_fence();
+  return sh;
+}
+
 #ifndef AVM_BUSY_PRIO
 #define AVM_BUSY_PRIO 1
 #endif
-#ifndef AVM_IDLE_NAP
-#define AVM_IDLE_NAP 16
-#endif
-#ifndef AVM_IDLE_MAX_NAPS
-#define AVM_IDLE_MAX_NAPS 63
-#endif
+
+// Waves that carry few electrons.  A lone electron's flight is a chain of
+// instructions; at most kFewLanes electrons get their random numbers drawn
+// ahead by all lanes (RandWave).  An empty wave naps between looks at its
+// claim: up to kIdleMaxNaps x kIdleNap x 64 cycles (1.7 us), kIdlePolls
+// looks between two tests for the run's end.  While at most half of the
+// waves carry electrons and the run has not filled the device yet (7/8 of
+// the waves busy), or at most 1/8 carry some, a wave keeps kSpread electrons
+// and hands further secondaries to the waves without any: a wave of one
+// electron makes a flight in 0.98 us, one of eight in 1.15, one of 64 in
+// 1.73 (FP64 slab).  Once the device was full, secondaries stay in their
+// wave: spread over waves that share a SIMD they cost more issue slots (1000
+// avalanches 15.8 -> 17.0 ms).  A block's waves come to the queue kStagger
+// naps apart.
+constexpr int kFewLanes = 32;
+constexpr int kFewPass = 4;  // passes such a wave runs in one when no lane stops
+constexpr uint32_t kSpread = 4;
+constexpr int kIdleNap = 16, kIdleMaxNaps = 4, kIdlePolls = 8, kStagger = 4;
 
 // Occupancy target of the persistent kernel (waves per SIMD); the register
 // budget follows from it.
@@ -547,13 +630,16 @@ struct Xfer {
 //      `tail`, which so counts every electron created, before any of them
 //      can be seen by another wave);
 //   2. hands secondaries to its own idle lanes through LDS (ballot/mbcnt
-//      ranks: the k-th secondary goes to the k-th idle lane);
+//      ranks: the k-th secondary goes to the k-th idle lane), as many as it
+//      keeps (kSpread while few waves carry electrons);
 //   3. publishes the remaining secondaries on the global queue (one atomic
 //      on qtail; records written device-coherent, then the entry's ready
 //      word after the record stores are acknowledged);
 //   4. counts its terminated (and dropped) electrons locally;
 //   5. lets its still-idle lanes claim queue entries (one atomic on qhead)
-//      and picks up entries whose ready word shows the run's epoch.
+//      and picks up entries whose ready word shows the run's epoch; without
+//      an electron it takes its share of the queue, or claims one entry yet
+//      to be published and waits at that entry's ready word.
 // A wave that holds no electron adds its local count to `ended` (one
 // atomic), so `ended` never exceeds the number of electrons terminated.
 // Reading `ended` and then `tail` and finding them equal means every
@@ -613,11 +699,19 @@ __global__ void __launch_bounds__(kPBlock)
   bool has = false, cp = false;
   bool clear = false;  // the lane's next flight does not end its electron (finish_exit)
   unsigned long long n_gone = 0;  // electrons this wave terminated or dropped, not yet in `ended`
-  int idle_naps = 0;  // a wave with no electron backs off, longer the longer it stays idle
+  bool counted = false;  // this wave carries electrons and is counted in ctr->busy
+  bool spread = false;   // few waves were busy at the last look
+  bool filled = false;   // nearly all were at some look
+  const uint32_t n_waves = gridDim.x * (uint32_t)(kPBlock / 64);
+  const uint32_t wave_bits = 31u - (uint32_t)__builtin_clz(n_waves);
   unsigned long long claim = kNone;
   uint32_t slot = 0;
   Elec<R> e;
   Child<R> child;
+  // a block's waves come to the queue one after the other, so that few
+  // primaries spread over all CUs (a claim is only ever taken by a wave that
+  // runs: blocks that wait for a CU hold none)
+  for (uint32_t i = 0; i < (threadIdx.x >> 6) * kStagger; ++i) __builtin_amdgcn_s_sleep(kIdleNap);
   const uint64_t t_start = wall_clock64();
   for (;;) {
     if (wall_clock64() - t_start > P.budget_ticks) {
@@ -628,8 +722,28 @@ __global__ void __launch_bounds__(kPBlock)
     // ---- transport pass
     uint32_t term = 0;  // status of this lane's electron if it terminated in this pass
     int32_t r = has ? STEP_CONTINUE : STEP_NONE;
-    for (int f = 0; f < flights_per_pass && r == STEP_CONTINUE; ++f)
-      r = flight_step<R, kBanded, kField, kSignal>(e, G, T, F, P, child, clear, RandInline<R>{}, &Q);
+    // a wave of few electrons flies on past the pass while none of them stops
+    // (a claim it holds waits for the pass to end)
+    const uint32_t n_start = __popcll(__ballot(has));
+    const int limit = n_start <= kFewLanes && !__ballot(claim != kNone) ? kFewPass * flights_per_pass
+                                                                              : flights_per_pass;
+    for (int f = 0; f < limit;) {
+      const uint64_t m = __ballot(r == STEP_CONTINUE);
+      if (!m || (f >= flights_per_pass && __popcll(m) != n_start)) break;
+      RandWave<R> rs{(const AVM_LDS Xfer*)&X, 0u, __popcll(m) <= kFewLanes};
+      int n = (f < flights_per_pass ? flights_per_pass : limit) - f;
+      if (rs.ahead) {
+        const uint32_t rank =
+            __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        const uint32_t sh = draw_ahead<R>((AVM_LDS Xfer*)&X, r == STEP_CONTINUE, m, rank, e, P, T);
+        rs.i = rank << sh;
+        n = min(n, 1 << sh);
+      }
+      f += n;
+      for (; n > 0 && r == STEP_CONTINUE; --n, ++rs.i)
+        r = flight_step<R, kBanded, kField, kSignal>(e, G, T, F, P, child, clear, rs, &Q);
+      wave_fence();
+    }
     cp = r == STEP_IONISED;
     // ---- flights of this pass that may end their electron, settled together
     if (r == STEP_EXIT) {
@@ -661,7 +775,12 @@ __global__ void __launch_bounds__(kPBlock)
     n_gone += __popcll(__ballot(term != 0)) + __popcll(__ballot(cp && !stored));
     const uint64_t m_idle = __ballot(!has && claim == kNone);
     const uint32_t n_child = __popcll(m_child), n_idle = __popcll(m_idle);
-    const uint32_t n_match = n_child < n_idle ? n_child : n_idle;
+    uint32_t n_match = n_child < n_idle ? n_child : n_idle;
+    if (spread) {  // waves without an electron wait: keep few here
+      const uint32_t n_has = __popcll(__ballot(has));
+      const uint32_t room = n_has < kSpread ? kSpread - n_has : 0u;
+      n_match = n_match < room ? n_match : room;
+    }
     const uint32_t rank_c = __builtin_amdgcn_mbcnt_hi((uint32_t)(m_child >> 32),
                                                       __builtin_amdgcn_mbcnt_lo((uint32_t)m_child, 0u));
     const uint32_t rank_i = __builtin_amdgcn_mbcnt_hi((uint32_t)(m_idle >> 32),
@@ -719,9 +838,15 @@ __global__ void __launch_bounds__(kPBlock)
     if (m_want) {
       const unsigned long long qt = ld_coh_int(&ctr->qtail);
       const unsigned long long qh = ld_coh_int(&ctr->qhead);
+      const unsigned long long busy = ld_coh_int(&ctr->busy);
+      filled = filled || busy * 8 > 7ull * n_waves;
+      spread = busy * (filled ? 8 : 2) <= n_waves;
       const unsigned long long avail = qt > qh ? qt - qh : 0ull;
       const uint32_t n_want = __popcll(m_want);
-      const uint32_t n_take = avail < n_want ? (uint32_t)avail : n_want;
+      // a wave without an electron takes its share of the queue, rounded up
+      const unsigned long long share = __ballot(has || take) == 0 ? (avail >> wave_bits) + 1ull : ~0ull;
+      const unsigned long long most = avail < share ? avail : share;
+      const uint32_t n_take = most < n_want ? (uint32_t)most : n_want;
       if (n_take) {
         const uint32_t rk = __builtin_amdgcn_mbcnt_hi((uint32_t)(m_want >> 32),
                                                       __builtin_amdgcn_mbcnt_lo((uint32_t)m_want, 0u));
@@ -769,19 +894,30 @@ __global__ void __launch_bounds__(kPBlock)
       if (n_end == ld_coh_int(&ctr->tail + (n_end >> 63))) break;
     }
     if (__ballot(has) == 0) {
-      // nothing to carry: leave the SIMD to busy waves for a while before
-      // polling the queue again (the polls and the exchange code would
-      // otherwise take their issue slots)
+      // nothing to carry: hold one claim, so that the next entry published
+      // comes here, and wait for it with few instructions and, after each
+      // nap, one load of the entry's own ready word
 #if AVM_BUSY_PRIO
       __builtin_amdgcn_s_setprio(0);
 #endif
-      idle_naps = idle_naps < AVM_IDLE_MAX_NAPS ? 2 * idle_naps + 1 : AVM_IDLE_MAX_NAPS;
-      for (int i = 0; i < idle_naps; ++i) __builtin_amdgcn_s_sleep(AVM_IDLE_NAP);
+      const bool claims = __ballot(claim != kNone) != 0;
+      if (lane == 0) {
+        if (!claims)
+          claim = __hip_atomic_fetch_add(&ctr->qhead, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (counted) __hip_atomic_fetch_add(&ctr->busy, ~0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      counted = false;
+      for (int i = 0; i < kIdlePolls; ++i) {
+        if (__ballot(claim < S.capacity && ld_coh_int(&S.qready[claim]) == epoch)) break;
+        for (int j = 0; j <= i && j < kIdleMaxNaps; ++j) __builtin_amdgcn_s_sleep(kIdleNap);
+      }
     } else {
 #if AVM_BUSY_PRIO
       __builtin_amdgcn_s_setprio(2);
 #endif
-      idle_naps = 0;
+      if (!counted && lane == 0)
+        __hip_atomic_fetch_add(&ctr->busy, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      counted = true;
     }
   }
   // the wave's accumulated statistics go out; once every wave of the block
