@@ -13,15 +13,11 @@ namespace avm {
 static_assert(sizeof(avm_end_record) == 72 && alignof(avm_end_record) == 8, "end record layout");
 
 // Flights a lane makes between two visits of its wave to the queue when the
-// caller leaves it at 0, by precision.  Same-box sweeps on the slab
-// workloads: in FP64, 40 is 1.6-1.8 % faster than 32 (44 no better); in
-// FP32-mixed, whose flight steps are shorter, 48 is 1-2.6 % faster than 40
-// (56 no better).  The wire chamber is flat from 24 to 48 in both.
-constexpr int32_t kDefaultFlightsPerPass = 40;
-constexpr int32_t kDefaultFlightsPerPassF32 = 48;
-inline int32_t default_flights_per_pass(int32_t precision) {
-  return precision == AVM_FP32_MIXED ? kDefaultFlightsPerPassF32 : kDefaultFlightsPerPass;
-}
+// caller leaves it at 0 (half as many while the queue is long, see the
+// persistent kernel).  Same-box sweep with that halving, 40 / 48: 1000
+// avalanches 15.9 / 15.6 ms, 8192 avalanches 416 / 414 ms, high gain 30.3 /
+// 29.5 ms; FP32-mixed 12.4 / 12.4, 308 / 312 and 24.0 / 23.6 ms.
+constexpr int32_t kDefaultFlightsPerPass = 48;
 
 // Per-avalanche statistics (and totals, with the status histogram).
 struct AvalStats {

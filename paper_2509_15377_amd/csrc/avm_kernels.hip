@@ -510,7 +510,23 @@ AVM_FN T ld_coh_int(const T* p) {
 // wait until every store this wave issued has been acknowledged
 AVM_FN void wait_stores() { __builtin_amdgcn_s_waitcnt(0x0F70); /* vmcnt(0) */ }
 
-// Child records handed from a lane to an idle lane of the same wave.
+// Electrons that wait in their wave for an idle lane: a ring in LDS, served
+// oldest first, of secondaries born in the wave and entries claimed from the
+// queue.  An atomic on one of the run's counters takes 12 ns whichever wave
+// it comes from, and a claimed record comes after three dependent loads: a
+// wave that hands on and takes single electrons pays both in every pass.
+// While the queue is long (kLongQueue entries per wave) a wave keeps what its
+// ring holds and claims kReserve entries more than it needs, so most passes
+// touch neither the queue nor another wave; passes are then half as long,
+// which leaves fewer lanes idle behind an ended electron.  With a short queue
+// the ring keeps kKeep of the wave's own secondaries, and none while other
+// waves have no work.  The newest leave first; only secondaries born here
+// are published, so an electron is published once at most and the queue needs
+// no more entries than the run holds electrons: claimed entries come in only
+// while the ring holds fewer than kRingClaims.  Same box: 8192 avalanches
+// 460 -> 414 ms (FP32-mixed 369 -> 312), high gain of 64 avalanches 33.2 ->
+// 29.5 ms (28.0 -> 23.6), 1000 avalanches 16.1 -> 15.6 ms.
+constexpr uint32_t kLongQueue = 4, kKeep = 8, kReserve = 24, kRingClaims = 56;
 struct Xfer {
   double x[64], y[64], z[64], t[64], vx[64], vy[64], vz[64];
   uint64_t eid[64];
@@ -557,6 +573,54 @@ AVM_FN void wave_fence() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Rank of this lane in mask m (the number of set bits below it).
+AVM_FN uint32_t mask_rank(uint64_t m) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// Mask of the n ring positions from `from`.
+AVM_FN uint64_t ring_bits(uint32_t from, uint32_t n) {
+  const uint64_t m = n < 64u ? (1ull << n) - 1ull : ~0ull;
+  const uint32_t k = from & 63u;
+  return k ? (m << k) | (m >> (64u - k)) : m;
+}
+
+// The part of a secondary's start record that waits until it leaves the
+// ring (publish() writes it device-coherent, with the start velocity).
+AVM_FN void write_place(const Store& S, uint32_t s, double x, double y, double z, double t, uint64_t eid,
+                        uint32_t aval) {
+  S.x0[s] = x; S.y0[s] = y; S.z0[s] = z; S.t0[s] = t;
+  S.eid[s] = eid;
+  S.aval[s] = aval;
+}
+
+// Number of the ring's newest entries that were born in this wave.
+AVM_FN uint32_t born_last(uint64_t born, uint32_t h, uint32_t n) {
+  const uint32_t k = (h + n) & 63u;
+  const uint64_t x = ~(k ? (born << (64u - k)) | (born >> k) : born);  // bit 63: the newest
+  return min(n, x ? (uint32_t)__builtin_clzll(x) : 64u);
+}
+
+// Publishes k ring entries from `from` on the global queue (called by every
+// lane of the wave).  Other waves read the records, so they go out
+// device-coherent, and the entries' ready words after they are acknowledged.
+AVM_FN void publish(const Store& S, const Xfer& X, Counters* ctr, uint32_t from, uint32_t k, uint32_t epoch) {
+  const uint32_t lane = __lane_id();
+  unsigned long long q = 0;
+  if (lane == 0) q = __hip_atomic_fetch_add(&ctr->qtail, (unsigned long long)k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  q = __shfl(q, 0) + lane;
+  if (lane < k) {
+    const uint32_t i = (from + lane) & 63u, s = X.slot[i];
+    st_coh(&S.x0[s], X.x[i]); st_coh(&S.y0[s], X.y[i]); st_coh(&S.z0[s], X.z[i]); st_coh(&S.t0[s], X.t[i]);
+    st_coh(&S.vx0[s], X.vx[i]); st_coh(&S.vy0[s], X.vy[i]); st_coh(&S.vz0[s], X.vz[i]);
+    st_coh(&S.eid[s], X.eid[i]);
+    st_coh(&S.aval[s], X.aval[i]);
+    st_coh(&S.qslot[q], s);
+  }
+  wait_stores();
+  if (lane < k) st_coh(&S.qready[q], epoch);
 }
 
 // Draws the flights ahead of the lanes with `live` (m = their ballot, not
@@ -629,17 +693,19 @@ constexpr int kIdleNap = 16, kIdleMaxNaps = 4, kIdlePolls = 8, kStagger = 4;
 //   1. allocates storage slots for its new secondaries (one atomic on
 //      `tail`, which so counts every electron created, before any of them
 //      can be seen by another wave);
-//   2. hands secondaries to its own idle lanes through LDS (ballot/mbcnt
-//      ranks: the k-th secondary goes to the k-th idle lane), as many as it
-//      keeps (kSpread while few waves carry electrons);
-//   3. publishes the remaining secondaries on the global queue (one atomic
-//      on qtail; records written device-coherent, then the entry's ready
-//      word after the record stores are acknowledged);
+//   2. puts its secondaries into its ring in LDS (a full ring publishes its
+//      newest on the global queue: one atomic on qtail; records written
+//      device-coherent, then the entries' ready words after the record
+//      stores are acknowledged);
+//   3. claims queue entries for the idle lanes the ring leaves (one atomic on
+//      qhead) and loads entries whose ready word shows the run's epoch into
+//      the ring; without an electron it takes its share of the queue, or
+//      claims one entry yet to be published and waits at its ready word;
 //   4. counts its terminated (and dropped) electrons locally;
-//   5. lets its still-idle lanes claim queue entries (one atomic on qhead)
-//      and picks up entries whose ready word shows the run's epoch; without
-//      an electron it takes its share of the queue, or claims one entry yet
-//      to be published and waits at that entry's ready word.
+//   5. lets its idle lanes take the ring's oldest entries (ballot/mbcnt
+//      ranks: the k-th idle lane takes the k-th entry), as many as it keeps
+//      (kSpread while few waves carry electrons);
+//   6. publishes what the ring should not keep.
 // A wave that holds no electron adds its local count to `ended` (one
 // atomic), so `ended` never exceeds the number of electrons terminated.
 // Reading `ended` and then `tail` and finding them equal means every
@@ -700,11 +766,13 @@ __global__ void __launch_bounds__(kPBlock)
   bool clear = false;  // the lane's next flight does not end its electron (finish_exit)
   unsigned long long n_gone = 0;  // electrons this wave terminated or dropped, not yet in `ended`
   bool counted = false;  // this wave carries electrons and is counted in ctr->busy
-  bool spread = false;   // few waves were busy at the last look
   bool filled = false;   // nearly all were at some look
   const uint32_t n_waves = gridDim.x * (uint32_t)(kPBlock / 64);
   const uint32_t wave_bits = 31u - (uint32_t)__builtin_clz(n_waves);
   unsigned long long claim = kNone;
+  bool long_queue = false;  // the queue held kLongQueue entries per wave at the last look
+  uint32_t ring_h = 0, ring_n = 0;  // the ring in the transfer buffer: oldest entry, number of entries
+  uint64_t ring_born = 0;           // entries born in this wave, whose start is not written yet
   uint32_t slot = 0;
   Elec<R> e;
   Child<R> child;
@@ -725,13 +793,13 @@ __global__ void __launch_bounds__(kPBlock)
     // a wave of few electrons flies on past the pass while none of them stops
     // (a claim it holds waits for the pass to end)
     const uint32_t n_start = __popcll(__ballot(has));
-    const int limit = n_start <= kFewLanes && !__ballot(claim != kNone) ? kFewPass * flights_per_pass
-                                                                              : flights_per_pass;
+    const int pass = long_queue ? (flights_per_pass + 1) / 2 : flights_per_pass;
+    const int limit = n_start <= kFewLanes && !__ballot(claim != kNone) ? kFewPass * pass : pass;
     for (int f = 0; f < limit;) {
       const uint64_t m = __ballot(r == STEP_CONTINUE);
-      if (!m || (f >= flights_per_pass && __popcll(m) != n_start)) break;
-      RandWave<R> rs{(const AVM_LDS Xfer*)&X, 0u, __popcll(m) <= kFewLanes};
-      int n = (f < flights_per_pass ? flights_per_pass : limit) - f;
+      if (!m || (f >= pass && __popcll(m) != n_start)) break;
+      RandWave<R> rs{(const AVM_LDS Xfer*)&X, 0u, ring_n == 0 && __popcll(m) <= kFewLanes};
+      int n = (f < pass ? pass : limit) - f;
       if (rs.ahead) {
         const uint32_t rank =
             __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
@@ -771,111 +839,113 @@ __global__ void __launch_bounds__(kPBlock)
     const unsigned long long cs = wave_alloc(&ctr->tail, cp);
     const bool stored = cp && cs < S.capacity;
     const uint64_t m_child = __ballot(stored);
+    const uint32_t n_child = __popcll(m_child);
     // 4. terminations and dropped secondaries of this pass
     n_gone += __popcll(__ballot(term != 0)) + __popcll(__ballot(cp && !stored));
-    const uint64_t m_idle = __ballot(!has && claim == kNone);
-    const uint32_t n_child = __popcll(m_child), n_idle = __popcll(m_idle);
-    uint32_t n_match = n_child < n_idle ? n_child : n_idle;
-    if (spread) {  // waves without an electron wait: keep few here
-      const uint32_t n_has = __popcll(__ballot(has));
-      const uint32_t room = n_has < kSpread ? kSpread - n_has : 0u;
-      n_match = n_match < room ? n_match : room;
-    }
-    const uint32_t rank_c = __builtin_amdgcn_mbcnt_hi((uint32_t)(m_child >> 32),
-                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)m_child, 0u));
-    const uint32_t rank_i = __builtin_amdgcn_mbcnt_hi((uint32_t)(m_idle >> 32),
-                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)m_idle, 0u));
-    const bool local = stored && rank_c < n_match;
-    // 3. queue entries for the secondaries no idle lane of this wave takes
-    const unsigned long long q = wave_alloc(&ctr->qtail, stored && !local);
+    // the queue and the other waves, as they are now
+    const unsigned long long qt = ld_coh_int(&ctr->qtail);
+    const unsigned long long qh = ld_coh_int(&ctr->qhead);
+    const unsigned long long busy = ld_coh_int(&ctr->busy);
+    const unsigned long long avail = qt > qh ? qt - qh : 0ull;
+    long_queue = avail >= (unsigned long long)kLongQueue * n_waves;
+    filled = filled || busy * 8 > 7ull * n_waves;
+    const bool spread = busy * (filled ? 8 : 2) <= n_waves;
+    // 2. secondaries wait in the ring; when it is full its newest go to the
+    //    queue (they were born here: claimed entries come in only while
+    //    kRingClaims are taken at most)
     if (stored) {
-      // start record: the electron's output; queued ones are also read by
-      // other waves, so those go out device-coherent
-      if (local) {
-        // (the start velocity goes through LDS: only queued electrons need
-        // it in memory)
-        S.x0[cs] = e.x; S.y0[cs] = e.y; S.z0[cs] = e.z; S.t0[cs] = e.t;
-        S.eid[cs] = child.eid;
-        S.aval[cs] = e.aval;
-        X.x[rank_c] = e.x; X.y[rank_c] = e.y; X.z[rank_c] = e.z; X.t[rank_c] = e.t;
-        X.vx[rank_c] = (double)child.vx; X.vy[rank_c] = (double)child.vy;
-        X.vz[rank_c] = (double)child.vz;
-        X.eid[rank_c] = child.eid;
-        X.slot[rank_c] = (uint32_t)cs;
-        X.aval[rank_c] = e.aval;
-      } else {
-        st_coh(&S.x0[cs], e.x); st_coh(&S.y0[cs], e.y); st_coh(&S.z0[cs], e.z); st_coh(&S.t0[cs], e.t);
-        st_coh(&S.vx0[cs], (double)child.vx); st_coh(&S.vy0[cs], (double)child.vy);
-        st_coh(&S.vz0[cs], (double)child.vz);
-        st_coh(&S.eid[cs], child.eid);
-        st_coh(&S.aval[cs], e.aval);
-        st_coh(&S.qslot[q], (uint32_t)cs);
-      }
       S.e0[cs] = (double)child.e;
       S.parent[cs] = e.eid;
     }
-    // publish queue entries once their records are acknowledged
-    wait_stores();
-    if (stored && !local) st_coh(&S.qready[q], epoch);
-    // 2. idle lanes of this wave take the local secondaries
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const bool take = (m_idle >> lane & 1) && rank_i < n_match;
-    if (take) {
-      e.x = X.x[rank_i]; e.y = X.y[rank_i]; e.z = X.z[rank_i]; e.t = X.t[rank_i];
-      e.vx = (R)X.vx[rank_i]; e.vy = (R)X.vy[rank_i]; e.vz = (R)X.vz[rank_i];
-      e.eid = X.eid[rank_i];
-      e.aval = X.aval[rank_i];
-      slot = X.slot[rank_i];
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // 5. still-idle lanes claim queue entries while the queue has some
-    const bool want = !has && claim == kNone && !take;
-    const uint64_t m_want = __ballot(want);
-    if (m_want) {
-      const unsigned long long qt = ld_coh_int(&ctr->qtail);
-      const unsigned long long qh = ld_coh_int(&ctr->qhead);
-      const unsigned long long busy = ld_coh_int(&ctr->busy);
-      filled = filled || busy * 8 > 7ull * n_waves;
-      spread = busy * (filled ? 8 : 2) <= n_waves;
-      const unsigned long long avail = qt > qh ? qt - qh : 0ull;
-      const uint32_t n_want = __popcll(m_want);
-      // a wave without an electron takes its share of the queue, rounded up
-      const unsigned long long share = __ballot(has || take) == 0 ? (avail >> wave_bits) + 1ull : ~0ull;
-      const unsigned long long most = avail < share ? avail : share;
-      const uint32_t n_take = most < n_want ? (uint32_t)most : n_want;
-      if (n_take) {
-        const uint32_t rk = __builtin_amdgcn_mbcnt_hi((uint32_t)(m_want >> 32),
-                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)m_want, 0u));
-        unsigned long long base = 0;
-        if (want && rk == 0)
-          base = __hip_atomic_fetch_add(&ctr->qhead, (unsigned long long)n_take, __ATOMIC_RELAXED,
-                                        __HIP_MEMORY_SCOPE_AGENT);
-        base = __shfl(base, __builtin_ctzll(m_want));
-        if (want && rk < n_take) claim = base + rk;
+    const uint32_t rank_c = mask_rank(m_child);
+    for (uint32_t done = 0; done < n_child;) {
+      const uint32_t n = min(n_child - done, 64u - ring_n);
+      if (stored && rank_c - done < n) {
+        const uint32_t i = (ring_h + ring_n + rank_c - done) & 63u;
+        X.x[i] = e.x; X.y[i] = e.y; X.z[i] = e.z; X.t[i] = e.t;
+        X.vx[i] = (double)child.vx; X.vy[i] = (double)child.vy; X.vz[i] = (double)child.vz;
+        X.eid[i] = child.eid;
+        X.slot[i] = (uint32_t)cs;
+        X.aval[i] = e.aval;
+      }
+      ring_born |= ring_bits(ring_h + ring_n, n);
+      done += n;
+      ring_n += n;
+      wave_fence();
+      if (done < n_child) {
+        const uint32_t k = min(born_last(ring_born, ring_h, ring_n), 32u);
+        publish(S, X, ctr, ring_h + ring_n - k, k, epoch);
+        ring_n -= k;
       }
     }
-    if (take) {
+    // 3. claims of queue entries for the idle lanes that the ring leaves
+    //    (with a long queue, some for the next passes too)
+    const uint64_t m_idle = __ballot(!has);
+    const uint32_t n_idle = __popcll(m_idle);
+    // (waves without an electron wait: keep few here)
+    const uint32_t n_has = 64u - n_idle, room = !spread ? 64u : n_has < kSpread ? kSpread - n_has : 0u;
+    const uint64_t m_free = __ballot(claim == kNone);
+    const uint32_t n_held = ring_n + 64u - __popcll(m_free);
+    if (n_held < n_idle && avail) {
+      uint32_t n_take = n_idle - n_held + (long_queue ? kReserve : 0u);
+      n_take = min(n_take, 64u - n_held);
+      if (spread) n_take = min(n_take, room);
+      // a wave without an electron takes its share of the queue, rounded up
+      const unsigned long long share = n_idle == 64u && ring_n == 0u ? (avail >> wave_bits) + 1ull : avail;
+      n_take = share < n_take ? (uint32_t)share : n_take;
+      if (n_take) {
+        const uint32_t rk = mask_rank(m_free);
+        unsigned long long base = 0;
+        if (lane == 0)
+          base = __hip_atomic_fetch_add(&ctr->qhead, (unsigned long long)n_take, __ATOMIC_RELAXED,
+                                        __HIP_MEMORY_SCOPE_AGENT);
+        base = __shfl(base, 0);
+        if (claim == kNone && rk < n_take) claim = base + rk;
+      }
+    }
+    //    claimed entries that are published come into the ring
+    if (__ballot(claim != kNone)) {
+      const uint64_t m_ready = __ballot(claim < S.capacity && ld_coh_int(&S.qready[claim]) == epoch);
+      const uint32_t rk = mask_rank(m_ready);
+      const uint32_t n_ready = min((uint32_t)__popcll(m_ready), ring_n < kRingClaims ? kRingClaims - ring_n : 0u);
+      if ((m_ready >> lane & 1) && rk < n_ready) {
+        const uint32_t i = (ring_h + ring_n + rk) & 63u, s = ld_coh_int(&S.qslot[claim]);
+        X.slot[i] = s;
+        X.x[i] = ld_coh(&S.x0[s]); X.y[i] = ld_coh(&S.y0[s]); X.z[i] = ld_coh(&S.z0[s]);
+        X.t[i] = ld_coh(&S.t0[s]);
+        X.vx[i] = ld_coh(&S.vx0[s]); X.vy[i] = ld_coh(&S.vy0[s]); X.vz[i] = ld_coh(&S.vz0[s]);
+        X.eid[i] = ld_coh_int(&S.eid[s]);
+        X.aval[i] = ld_coh_int(&S.aval[s]);
+        claim = kNone;
+      }
+      ring_born &= ~ring_bits(ring_h + ring_n, n_ready);
+      ring_n += n_ready;
+    }
+    wave_fence();
+    // 5. idle lanes take the ring's oldest entries
+    const uint32_t n_pop = min(min(n_idle, ring_n), room);
+    const uint32_t rank_i = mask_rank(m_idle);
+    if (!has && rank_i < n_pop) {
+      const uint32_t i = (ring_h + rank_i) & 63u;
+      e.x = X.x[i]; e.y = X.y[i]; e.z = X.z[i]; e.t = X.t[i];
+      e.vx = (R)X.vx[i]; e.vy = (R)X.vy[i]; e.vz = (R)X.vz[i];
+      e.eid = X.eid[i];
+      e.aval = X.aval[i];
+      slot = X.slot[i];
+      if (ring_born >> i & 1) write_place(S, slot, e.x, e.y, e.z, e.t, e.eid, e.aval);
       load_elec_tail<R, kBanded, kField>(G, T, F, P, e);
       if (kSignal) signal_birth<R, kField>(Q, e);
       has = true;
-    } else if (!has && claim != kNone) {
-      if (claim < S.capacity && ld_coh_int(&S.qready[claim]) == epoch) {
-        slot = ld_coh_int(&S.qslot[claim]);
-        e.x = ld_coh(&S.x0[slot]); e.y = ld_coh(&S.y0[slot]); e.z = ld_coh(&S.z0[slot]);
-        e.t = ld_coh(&S.t0[slot]);
-        e.vx = (R)ld_coh(&S.vx0[slot]); e.vy = (R)ld_coh(&S.vy0[slot]);
-        e.vz = (R)ld_coh(&S.vz0[slot]);
-        e.eid = ld_coh_int(&S.eid[slot]);
-        e.aval = ld_coh_int(&S.aval[slot]);
-        load_elec_tail<R, kBanded, kField>(G, T, F, P, e);
-        if (kSignal) signal_birth<R, kField>(Q, e);
-        has = true;
-        claim = kNone;
-      }
+    }
+    ring_h = (ring_h + n_pop) & 63u;
+    ring_n -= n_pop;
+    wave_fence();
+    // 6. what is left goes to waves without work, if there are any
+    const uint32_t keep = busy * 8 < 7ull * n_waves ? 0u : long_queue ? 64u : kKeep;
+    if (ring_n > keep) {
+      const uint32_t k = min(born_last(ring_born, ring_h, ring_n), ring_n - keep);
+      if (k) publish(S, X, ctr, ring_h + ring_n - k, k, epoch);
+      ring_n -= k;
     }
     if (__ballot(has) == 0) {
       // no electron in this wave: flush the local count, then test for the
@@ -919,6 +989,11 @@ __global__ void __launch_bounds__(kPBlock)
         __hip_atomic_fetch_add(&ctr->busy, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       counted = true;
     }
+  }
+  // (out of time) electrons still in the ring: their starts
+  if (lane < ring_n) {
+    const uint32_t i = (ring_h + lane) & 63u;
+    if (ring_born >> i & 1) write_place(pinned(Sg), X.slot[i], X.x[i], X.y[i], X.z[i], X.t[i], X.eid[i], X.aval[i]);
   }
   // the wave's accumulated statistics go out; once every wave of the block
   // has left the loop, the block's totals

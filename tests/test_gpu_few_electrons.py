@@ -33,3 +33,31 @@ def test_batched_equals_plain(n, flights, precision):
     assert a.size >= n and a.tobytes() == b.tobytes()
     assert ca == cb
     assert all(np.array_equal(pa[k], pb[k]) for k in pa)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("n,flights", [(700, 0), (9000, 0), (9000, 200), (9000, 2)])
+def test_full_rings_and_long_queue(n, flights, precision):
+    """Many ionisations per pass (rings overflow, the queue gets long), and a
+    run whose capacity is exactly the number of its electrons."""
+    from paper_2509_15377_amd import avm, workloads as W
+    w = W.toy(n, band_bins=50)
+    for c in w.gas.channels:
+        if c.kind == W.IONISATION:
+            c.values = c.values * 20.0
+    w.field = W.slab(4e-4, 400e3)
+    g, f = avm.Gas(w.gas, 0), avm.Field(w.field, 0)
+
+    def go(mode, capacity, fpp):
+        r = avm.Run(g, f, w.primaries, n, seed=3, precision=precision, majorant=avm.BANDED, mode=mode,
+                    capacity=capacity, flights_per_pass=fpp, band_lookahead=1.0, timeout_s=60.0)
+        r.execute()
+        r.sync()
+        out = _sorted(r.endpoints()), r.counts(), r.avalanche_counts()
+        r.close()
+        return out
+    a, ca, pa = go(avm.PLAIN, 4 << 20, 0)
+    b, cb, pb = go(avm.BATCHED, a.size, flights)
+    assert a.size > 20 * n and a.tobytes() == b.tobytes()
+    assert ca == cb
+    assert all(np.array_equal(pa[k], pb[k]) for k in pa)
