@@ -106,6 +106,7 @@ struct GasDev {
 // depend on the view.
 template <class R>
 struct TabView {
+  static constexpr bool kStaged = false;
   const R* tot;
   const R* cum0;
   R x_lo;     // energies below x_lo bins have both nodes in tot and cum0 (n_lo - 1)
@@ -135,6 +136,7 @@ inline bool tables_fit_lds(const GasDev& G) { return G.n_bands <= kLdsBands && G
 
 template <class R>
 struct TabLds {
+  static constexpr bool kStaged = true;
   const AVM_LDS R* tot;
   const AVM_LDS R* cum0;
   R x_lo;
@@ -154,6 +156,7 @@ struct TabLds {
 // here, so that a comparison with an edge that does not exist is false.
 template <class R>
 struct TabFit {
+  static constexpr bool kStaged = true;
   const AVM_LDS R* tot;
   const AVM_LDS R* cum0;
   R x_lo;
@@ -447,6 +450,7 @@ template <> struct M<double> {
   AVM_FN static double atan_(double x) { return atan(x); }
   AVM_FN static void sincospi_(double x, double* s, double* c) { sincospi_pos(x, s, c); }
   AVM_FN static double abs_(double x) { return fabs(x); }
+  AVM_FN static double min_(double x, double y) { return __builtin_fmin(x, y); }  // y for a NaN x
   AVM_FN static double inf() { return __builtin_inf(); }
   // the sampling and scattering forms (flight-time logarithm, scattering
   // and emission angles, speeds): the accurate ones in FP64
@@ -466,6 +470,7 @@ template <> struct M<float> {
   AVM_FN static float atan_(float x) { return atanf(x); }
   AVM_FN static void sincospi_(float x, float* s, float* c) { sincospif(x, s, c); }
   AVM_FN static float abs_(float x) { return fabsf(x); }
+  AVM_FN static float min_(float x, float y) { return __builtin_fminf(x, y); }
   AVM_FN static float inf() { return __builtin_inff(); }
   AVM_FN static float sqrt_0(float x) {  // sqrt_s, 0 for x <= 0
     const float r = sqrt_s(x);
@@ -532,28 +537,39 @@ AVM_FN void azimuth(const TV& T, double u, double* sp, double* cp) {
 template <class TV>
 AVM_FN void azimuth(const TV&, float u, float* sp, float* cp) { M<float>::sincos2pi_s(u, sp, cp); }
 
-// Direction of (dx, dy, dz) turned by polar angle theta (cos_t) and azimuth
-// phi = 2 pi u_phi.  The transverse length s = sqrt(dx^2 + dy^2) avoids the
-// cancellation of sqrt(1 - dz^2) next to the poles, so |d'| = 1 to rounding.
-// sp, cp: sin and cos of phi.
+// The enclosing branch is rare: keeps the compiler from turning it into
+// selects, which every lane would pay for.
+AVM_FN void rare_branch() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("");
+#endif
+}
+
+// Direction of the velocity (vx, vy, vz) (at rest: the z axis) turned by polar
+// angle theta (cos_t) and azimuth phi (its sine sp and cosine cp).  The
+// transverse length s = sqrt(dx^2 + dy^2) avoids the cancellation of
+// sqrt(1 - dz^2) next to the poles, so the result has unit length to rounding.
 template <class R>
-AVM_FN void turn(R sp, R cp, R dx, R dy, R dz, R cos_t, R& ox, R& oy, R& oz) {
+AVM_FN void turn(R sp, R cp, R vx, R vy, R vz, R cos_t, R& ox, R& oy, R& oz) {
+  const R v2 = dot3<R>(vx, vy, vz, vx, vy, vz);
+  const R inv = M<R>::rsqrt_s(v2);
+  const R dx = vx * inv, dy = vy * inv, dz = vz * inv;
   const R st2 = M<R>::fma(-cos_t, cos_t, R(1));
   const R sin_t = M<R>::sqrt_0(st2);
   const R q = M<R>::fma(dx, dx, dy * dy);
   const R tiny = sizeof(R) == 8 ? R(1e-24) : R(1e-12);
-  // (the general form is evaluated in any case; its values are not used next
-  // to the poles, where it may not be finite)
   const R inv_s = M<R>::rsqrt_s(q);
   const R s = q * inv_s;
   const R a = sin_t * inv_s;
   ox = M<R>::fma(dx, cos_t, a * M<R>::fma(dx * dz, cp, -dy * sp));
   oy = M<R>::fma(dy, cos_t, a * M<R>::fma(dy * dz, cp, dx * sp));
   oz = M<R>::fma(dz, cos_t, -s * sin_t * cp);
-  if (!(q > tiny)) {
+  if (!(v2 > R(0) && q > tiny)) {
+    // at rest or next to the poles (the form above may not be finite there)
+    rare_branch();
     ox = sin_t * cp;
     oy = sin_t * sp;
-    oz = (dz < R(0) ? R(-1) : R(1)) * cos_t;
+    oz = (v2 > R(0) && dz < R(0) ? R(-1) : R(1)) * cos_t;
   }
 }
 
@@ -872,8 +888,7 @@ AVM_FN int32_t band_of_tabs(const GasDev& G, const TV& T, R e, R& gam, R& inv, R
 // branch.  (A guess is below n_bands also for an infinite or NaN energy.)
 template <class R>
 AVM_FN int32_t band_guess(const GasDev& G, R e) {
-  const R x = e * Sel<R>::band_scale(G), top = (R)(G.n_bands - 1);
-  return (int32_t)(uint32_t)(x < top ? x : top);
+  return (int32_t)(uint32_t)M<R>::min_(e * Sel<R>::band_scale(G), (R)(G.n_bands - 1));
 }
 template <class R>
 AVM_FN int32_t band_of(const GasDev& G, const TabFit<R>& T, R e) {
@@ -1141,16 +1156,8 @@ AVM_FN R band_crossing(const RunParams& P, const Elec<R>& e, R ax, R ay, R az, R
 // energy.  (The caller advances the flight index.)
 template <class R>
 AVM_FN void scatter_to(Elec<R>& e, const RunParams& P, R sp, R cp, R cos_t, R e_new) {
-  const R v2 = dot3<R>(e.vx, e.vy, e.vz, e.vx, e.vy, e.vz);
-  const R inv = M<R>::rsqrt_s(v2);
-  R dx = e.vx * inv, dy = e.vy * inv, dz = e.vz * inv;
-  if (!(v2 > R(0))) {  // at rest
-    dx = R(0);
-    dy = R(0);
-    dz = R(1);
-  }
   R ox, oy, oz;
-  turn<R>(sp, cp, dx, dy, dz, cos_t, ox, oy, oz);
+  turn<R>(sp, cp, e.vx, e.vy, e.vz, cos_t, ox, oy, oz);
   const R sp1 = M<R>::sqrt_s(Sel<R>::two_ka(P) * e_new);
   e.vx = sp1 * ox;
   e.vy = sp1 * oy;
@@ -1178,6 +1185,20 @@ AVM_FN int search_channel(const GasDev& G, int32_t kb, R f, R g1, bool over, R r
       lo = mid + 1;
   }
   return lo;
+}
+
+// The chosen channel: the smallest c with r_sel < interpolated cumulative
+// rate c (`above0`: r_sel is known to be no smaller than channel 0's).
+template <class R>
+AVM_FN int select_channel(const GasDev& G, bool above0, int32_t kb, R f, R g1, bool over, R r_sel, R& mg) {
+  if (!above0) {
+    const R* cz = Sel<R>::cum0(G);
+    const R c0 = over ? cz[kb] : lerp<R>(cz[kb], cz[kb + 1], g1, f);
+    const R dm = M<R>::abs_(r_sel - c0);
+    mg = dm < mg ? dm : mg;
+    if (r_sel < c0) return 0;
+  }
+  return search_channel<R>(G, kb, f, g1, over, r_sel, mg);
 }
 
 // Total rate and cumulative rate of channel 0 at x bins, from the global
@@ -1323,7 +1344,7 @@ AVM_FN uint32_t cylinder_exit(const Elec<R>& e, const FieldDev& F, R ax, R ay, R
 template <class R>
 AVM_FN bool slab_clear(const FieldDev& F, double z0, double z1, R w) {
   const double half = sizeof(R) == 8 ? F.z_half : F.z_half_f;
-  return __builtin_fma(0.5, fabs((double)w), fabs(z0 - F.z_mid)) < half && fabs(z1 - F.z_mid) < half;
+  return (__builtin_fma(0.5, fabs((double)w), fabs(z0 - F.z_mid)) < half) & (fabs(z1 - F.z_mid) < half);
 }
 
 // One pass of the loop for electron `e`.  Returns STEP_CONTINUE when the
@@ -1347,9 +1368,14 @@ AVM_FN bool slab_clear(const FieldDev& F, double z0, double z1, R w) {
 // one branch per outcome and searched bands: 665 -> about 560 vector
 // instructions per flight of a full wave; 8192 avalanches 505 -> 450 ms, one
 // avalanche 7.2 -> 5.7 ms (FP64), 1000 in FP32-mixed 15.5 -> 13.2 ms.
+// Lane masks carried over a branch or the loop cost three scalar instructions
+// each, so what only a rare path sets is a vector register (`clear`), tests
+// are not short-circuited, and the channels other than 0 end in one block:
+// with these a lone electron's flight takes 0.84 us instead of 0.98, 8192
+// avalanches 389 ms instead of 413.
 template <class R, bool kBanded, int kField, bool kSignal = false, class TV, class RS>
 AVM_FN int32_t flight_step(Elec<R>& e, const GasDev& G, const TV& T, const FieldDev& F,
-                           const RunParams& P, Child<R>& child, bool& clear, RS rs,
+                           const RunParams& P, Child<R>& child, uint32_t& clear, RS rs,
                            const SignalDev* Q = nullptr) {
   using Mr = M<R>;
   constexpr bool kMixed = sizeof(R) == 4;
@@ -1453,11 +1479,12 @@ AVM_FN int32_t flight_step(Elec<R>& e, const GasDev& G, const TV& T, const Field
   // the time and flight limits
   const double t_left = P.t_max - e.t;
   const double q0 = e.x * e.x + e.y * e.y, q1 = rx * rx + ry * ry;
-  bool go = t_left > (double)tau && e.k < P.k_max;
+  // (no short circuits: the tests are cheaper than branches)
+  bool go = (t_left > (double)tau) & (e.k < P.k_max);
   if (kField == FIELD_SLAB)
-    go = go && slab_clear<R>(F, e.z, rz, e.vz * tau);
+    go = go & slab_clear<R>(F, e.z, rz, e.vz * tau);
   else
-    go = go && q0 > F.a2 && q0 < F.b2 && q1 > F.a2 && q1 < F.b2;
+    go = go & (q0 > F.a2) & (q0 < F.b2) & (q1 > F.a2) & (q1 < F.b2);
   if (!go) {
     // near a boundary or a limit: the exact conditions
     go = !region_status<R, kField>(F, e) && e.k < P.k_max && !(e.t >= P.t_max) && !(t_left < (double)tau);
@@ -1465,8 +1492,8 @@ AVM_FN int32_t flight_step(Elec<R>& e, const GasDev& G, const TV& T, const Field
       go = go && slab_inside(e.z, (double)e.vz, (double)az, F.z_lo, F.z_hi, (double)tau);
     else
       go = go && !(q1 <= F.a2 || q1 >= F.b2);
-    if (clear) go = true;
-    clear = false;
+    go = go | (clear != 0);
+    clear = 0;
   }
   child.pen = tau;
   int32_t ret = STEP_EXIT;
@@ -1499,30 +1526,64 @@ AVM_FN int32_t flight_step(Elec<R>& e, const GasDev& G, const TV& T, const Field
         c0 = lerp<R>(T.cum0[kb], T.cum0[kb + 1], g1, f);
       } else {
         rates_global<R>(G, x, over, kb, f, nu_tot, c0);
+        if (TV::kStaged && !T.el0) c0 = R(-1);
         if (!(en < Mr::inf())) {
           ret = STEP_DONE + ST_ERROR;
           over = false;
-          nu_tot = R(-1);
+          nu_tot = c0 = R(-1);
         }
         if (!kMixed && over) e.n_over += 1;
       }
+      if (!TV::kStaged && !T.el0) c0 = R(-1);  // (staged: so in the table)
       const R r_sel = u2 * gam;
-      const bool first = r_sel < c0;
-      int c = r_sel < nu_tot ? 0 : -1;
-      R mg = Mr::abs_(r_sel - nu_tot);
-      if (kMixed && c == 0) {
-        const R dm = Mr::abs_(r_sel - c0);
-        mg = dm < mg ? dm : mg;
-      }
-      // a channel other than an elastic channel 0 (FP32-mixed: near zero
-      // energy its window's edge may be close)
-      bool wc = false;
-      if (c == 0 && !(first && T.el0 && (!kMixed || en > R(1e-30)))) {
-        if (!first) c = search_channel<R>(G, kb, f, R(1) - f, over, r_sel, mg);
-        const ChanP<R> cw = chan(G, T, c);
-        c = in_window(cw.e_lo, cw.e_hi, (double)en, c, wc);
-      }
+      // A channel c that is not an elastic channel 0 (-2 - c: masked): settles
+      // what does not scatter here, and says whether it scatters.
+      const auto other = [&](int c) -> bool {
+        if (c < 0) {
+          e.n_masked += 1;
+          e.trace = trace_step(e.trace, e.k, TRACE_MASKED + (uint32_t)(-2 - c));
+          return false;
+        }
+        const ChanP<R> ch = chan(G, T, c);
+        bool pending = ch.kind == CH_IONISATION;
+        if (ch.kind == CH_EXCITATION && ch.pen_prob > R(0)) {
+          // Penning transfer, decided by the first uniform of block 2: the
+          // excitation and its transfer electron are finished with the
+          // ionisations after the pass
+          const Block w2 = draw(P, e.aval, e.eid, e.k, 2);
+          pending = Mr::uni(w2.w0, w2.w1) < ch.pen_prob;
+        }
+        if (!pending && ch.kind != CH_ATTACHMENT) return true;
+        e.n_real += 1;
+        e.trace = trace_step(e.trace, e.k, (uint32_t)c);
+        if (pending) {
+          // finished by complete_ionisation() (the caller batches it)
+          child.pen = en;
+          child.pc = c;
+          ret = STEP_IONISED;
+        } else {
+          ret = STEP_DONE + ST_ATTACHED;
+        }
+        return false;
+      };
+      // channel 0 at once where it is elastic and acts at every energy (c0 is
+      // its rate, else -1, which no r_sel is below)
+      bool first = r_sel < c0;
+      const bool hit = r_sel < nu_tot;
+      int c = 0;
+      bool scatter = first;
       if (kMixed) {
+        c = hit ? 0 : -1;
+        R mg = Mr::abs_(r_sel - nu_tot);
+        const R dm = Mr::abs_(r_sel - c0);
+        mg = hit & (dm < mg) ? dm : mg;
+        bool wc = false;
+        first = first & (en > R(1e-30));  // near zero energy its window's edge may be close
+        if (hit & !first) {
+          c = select_channel<R>(G, T.el0, kb, f, R(1) - f, over, r_sel, mg);
+          const ChanP<R> cw = chan(G, T, c);
+          c = in_window(cw.e_lo, cw.e_hi, (double)en, c, wc);
+        }
         if (mg <= R(kCloseRel) * r_sel || wc) {
           // too close to call in FP32: decide again in FP64 for this state
           const double vx = (double)e.vx, vy = (double)e.vy, vz = (double)e.vz;
@@ -1530,54 +1591,30 @@ AVM_FN int32_t flight_step(Elec<R>& e, const GasDev& G, const TV& T, const Field
           c = decide_64(G, en64, rs.u2_64(P, e.aval, e.eid, e.k) * (double)gam, over);
         }
         if (over) e.n_over += 1;
+        scatter = (c == 0) & T.el0;
+        if ((c != -1) & !scatter) scatter = other(c);
+      } else if (hit & !first) {
+        R mg = R(0);
+        c = select_channel<R>(G, T.el0, kb, f, R(1) - f, over, r_sel, mg);
+        const ChanP<R> cw = chan(G, T, c);
+        bool wc;
+        c = in_window(cw.e_lo, cw.e_hi, (double)en, c, wc);
+        scatter = other(c);
       }
       R e_band = en;  // energy whose band the next flight starts in
-      if (c != -1) {
-        bool scatter = true;
-        if (!(c == 0 && T.el0)) {
-          if (c < 0) {
-            e.n_masked += 1;
-            e.trace = trace_step(e.trace, e.k, TRACE_MASKED + (uint32_t)(-2 - c));
-            scatter = false;
-          } else {
-            const ChanP<R> ch = chan(G, T, c);
-            bool pending = ch.kind == CH_IONISATION;
-            if (ch.kind == CH_EXCITATION && ch.pen_prob > R(0)) {
-              // Penning transfer, decided by the first uniform of block 2:
-              // the excitation and its transfer electron are finished with
-              // the ionisations after the pass
-              const Block w2 = draw(P, e.aval, e.eid, e.k, 2);
-              pending = Mr::uni(w2.w0, w2.w1) < ch.pen_prob;
-            }
-            if (pending) {
-              // finished by complete_ionisation() (the caller batches it)
-              child.pen = en;
-              child.pc = c;
-              ret = STEP_IONISED;
-              scatter = false;
-            }
-            if (ch.kind == CH_ATTACHMENT) {
-              ret = STEP_DONE + ST_ATTACHED;
-              scatter = false;
-            }
-          }
-        }
-        if (c >= 0) {
-          e.n_real += 1;
-          e.trace = trace_step(e.trace, e.k, (uint32_t)c);
-        }
-        if (scatter) {
-          // one form for elastic collisions and excitations: an elastic
-          // channel's loss, any other's mass ratio and screening are zero
-          const ChanP<R> ch = chan(G, T, c);
-          R uA, sphi, cphi;
-          rs.collision(T, P, e.aval, e.eid, e.k, uA, sphi, cphi);
-          const R cchi = R(1) - R(2) * uA / Mr::fma(R(1) - uA, en * ch.inv_screen8, R(1));
-          const R e_new = en * (R(1) - ch.el_loss * (R(1) - cchi)) - ch.loss;
-          const R lab = (ch.mu + cchi) * Mr::rsqrt_s(Mr::fma(ch.two_mu, cchi, ch.mu2p1));
-          scatter_to<R>(e, P, sphi, cphi, ch.kind == CH_ELASTIC ? lab : cchi, e_new);
-          e_band = e_new;
-        }
+      if (scatter) {
+        // one form for elastic collisions and excitations: an elastic
+        // channel's loss, any other's mass ratio and screening are zero
+        e.n_real += 1;
+        e.trace = trace_step(e.trace, e.k, (uint32_t)c);
+        const ChanP<R> ch = chan(G, T, c);
+        R uA, sphi, cphi;
+        rs.collision(T, P, e.aval, e.eid, e.k, uA, sphi, cphi);
+        const R cchi = R(1) - R(2) * uA / Mr::fma(R(1) - uA, en * ch.inv_screen8, R(1));
+        const R e_new = en * (R(1) - ch.el_loss * (R(1) - cchi)) - ch.loss;
+        const R lab = (ch.mu + cchi) * Mr::rsqrt_s(Mr::fma(ch.two_mu, cchi, ch.mu2p1));
+        scatter_to<R>(e, P, sphi, cphi, ch.kind == CH_ELASTIC ? lab : cchi, e_new);
+        e_band = e_new;
       }
       // one band search for the null and the real-collision paths
       if (kBanded) band = band_of<R>(G, T, e_band);

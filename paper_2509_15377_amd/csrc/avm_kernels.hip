@@ -431,7 +431,7 @@ __global__ void __launch_bounds__(kBlock) k_generation(GasDev G, FieldDev F, Run
     e.ax = R(0); e.ay = R(0); e.az = R(0);
     if (kField == FIELD_SLAB) slab_field<R>(F, P, e);
     uint32_t status = 0;
-    bool clear = false;
+    uint32_t clear = 0;
     int32_t r;
     const uint64_t t_start = wall_clock64();
     uint32_t n = 0;
@@ -447,7 +447,7 @@ __global__ void __launch_bounds__(kBlock) k_generation(GasDev G, FieldDev F, Run
       // the lanes of the wave that may leave the volume are settled together
       if (r == STEP_EXIT) {
         status = finish_exit<R, kBanded, kField>(e, F, P, child.pen);
-        clear = status == 0;
+        clear = status == 0 ? 1u : 0u;
       }
     } while (clear);
     if (r >= STEP_DONE) status = (uint32_t)(r - STEP_DONE);
@@ -740,7 +740,7 @@ __global__ void __launch_bounds__(kPBlock)
   const int n_lo = G.n_bins + 1 < kLdsNodes ? G.n_bins + 1 : kLdsNodes;
   for (int k = threadIdx.x; k < n_lo; k += kPBlock) {
     s_tot[k] = Tg.tot[k];
-    s_cum0[k] = Tg.cum0[k];
+    s_cum0[k] = Tg.el0 ? Tg.cum0[k] : R(-1);  // (no r_sel is below: flight_step)
   }
   // the first kLdsBands bands and kLdsChannels channels (the accessors read
   // higher indices from the global arrays)
@@ -763,7 +763,7 @@ __global__ void __launch_bounds__(kPBlock)
   Xfer& X = xfer_all[threadIdx.x >> 6];
   const uint32_t lane = __lane_id();
   bool has = false, cp = false;
-  bool clear = false;  // the lane's next flight does not end its electron (finish_exit)
+  uint32_t clear = 0;  // the lane's next flight does not end its electron (finish_exit)
   unsigned long long n_gone = 0;  // electrons this wave terminated or dropped, not yet in `ended`
   bool counted = false;  // this wave carries electrons and is counted in ctr->busy
   bool filled = false;   // nearly all were at some look
@@ -816,7 +816,7 @@ __global__ void __launch_bounds__(kPBlock)
     // ---- flights of this pass that may end their electron, settled together
     if (r == STEP_EXIT) {
       term = finish_exit<R, kBanded, kField, kSignal>(e, F, P, child.pen, &Q);
-      clear = term == 0;
+      clear = term == 0 ? 1u : 0u;
     }
     if (r >= STEP_DONE) term = (uint32_t)(r - STEP_DONE);
     has = has && term == 0;
