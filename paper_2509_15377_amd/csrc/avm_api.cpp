@@ -1234,7 +1234,7 @@ hipError_t tune_key(const avm_gas* g, const avm_field* fl, const avm_primary* pr
 // Version of the cache lines: raised whenever the transport kernel changes
 // enough that an earlier timing no longer ranks the candidates right, so
 // that lines from an older library are ignored (and a new choice appended).
-constexpr int kTuneLineVersion = 5;
+constexpr int kTuneLineVersion = 6;
 
 bool cache_lookup(const char* path, uint64_t key, int* fpp, int* wpc, int* bb, float* look, double* ms) {
   if (!path) return false;
