@@ -914,8 +914,14 @@ __global__ void __launch_bounds__(kPBlock)
       uint32_t n_take = n_idle - n_held + (long_queue ? kReserve : 0u);
       n_take = min(n_take, 64u - n_held);
       if (spread) n_take = min(n_take, room);
-      // a wave without an electron takes its share of the queue, rounded up
-      const unsigned long long share = n_idle == 64u && ring_n == 0u ? (avail >> wave_bits) + 1ull : avail;
+      // a wave without an electron takes the share of one in 1/4 of the waves,
+      // rounded up: a short queue still goes one by one to waves of their own,
+      // a longer one to a wave per SIMD.  With one electron for each of more
+      // waves the SIMDs' issue slots run out at waves a third full (the whole
+      // shares against these, FP64 wire chamber: 2048 electrons 473 -> 345 ms,
+      // 1200 296 -> 268, 512 and 64 the same, shares of 1/64 of the waves
+      // 5 % slower there; 1000 avalanches the same)
+      const unsigned long long share = n_idle == 64u && ring_n == 0u ? (avail >> (wave_bits - 2u)) + 1ull : avail;
       n_take = share < n_take ? (uint32_t)share : n_take;
       if (n_take) {
         const uint32_t rk = mask_rank(m_free);
