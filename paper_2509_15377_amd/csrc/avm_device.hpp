@@ -1585,7 +1585,8 @@ AVM_FN int32_t flight_step(Elec<R>& e, const GasDev& G, const TV& T, const Field
         bool wc = false;
         first = first & (en > R(1e-30));  // near zero energy its window's edge may be close
         if (hit & !first) {
-          c = select_channel<R>(G, T.el0, kb, f, R(1) - f, over, r_sel, mg);
+          // (at rest also an electron whose r_sel is below c0 comes here)
+          c = select_channel<R>(G, T.el0 & !(r_sel < c0), kb, f, R(1) - f, over, r_sel, mg);
           const ChanP<R> cw = chan(G, T, c);
           c = in_window(cw.e_lo, cw.e_hi, (double)en, c, wc);
         }
