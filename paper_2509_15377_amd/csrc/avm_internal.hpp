@@ -19,6 +19,21 @@ static_assert(sizeof(avm_end_record) == 72 && alignof(avm_end_record) == 8, "end
 // 29.5 ms; FP32-mixed 12.4 / 12.4, 308 / 312 and 24.0 / 23.6 ms.
 constexpr int32_t kDefaultFlightsPerPass = 48;
 
+// Passes that a wave of few electrons flies in one while no lane stops.
+constexpr int32_t kFewPass = 4;
+
+// Flights of a pass.  The caller's number is any positive one; more than
+// kMaxFlightsPerPass are taken as that many (an electron makes fewer than
+// 2^30 flights, and no result depends on where its passes end), so that the
+// longest pass fits an int32_t.
+constexpr int32_t kMaxFlightsPerPass = 1 << 28;
+static_assert(kMaxFlightsPerPass <= INT32_MAX / kFewPass, "longest pass overflows");
+inline int32_t clamp_flights_per_pass(int32_t n) { return n < kMaxFlightsPerPass ? n : kMaxFlightsPerPass; }
+AVM_FN int32_t pass_flights(int32_t flights_per_pass, bool long_queue) {
+  return long_queue ? (flights_per_pass + 1) / 2 : flights_per_pass;
+}
+AVM_FN int32_t pass_limit(int32_t pass, bool few) { return few ? kFewPass * pass : pass; }
+
 // Per-avalanche statistics (and totals, with the status histogram).
 struct AvalStats {
   unsigned long long c[8];  // endpoints, ionisations, attachments, real, null, masked, band cuts, overflows

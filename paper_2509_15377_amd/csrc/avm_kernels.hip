@@ -583,7 +583,6 @@ AVM_FN uint32_t draw_ahead(AVM_LDS Xfer* X, bool live, uint64_t m, uint32_t rank
 // avalanches 15.8 -> 17.0 ms).  A block's waves come to the queue kStagger
 // naps apart.
 constexpr int kFewLanes = 32;
-constexpr int kFewPass = 4;  // passes such a wave runs in one when no lane stops
 constexpr uint32_t kSpread = 4;
 constexpr int kIdleNap = 16, kIdleMaxNaps = 4, kIdlePolls = 8, kStagger = 4;
 
@@ -817,8 +816,8 @@ __global__ void __launch_bounds__(kPBlock)
     // a wave of few electrons flies on past the pass while none of them stops
     // (a claim it holds waits for the pass to end)
     const uint32_t n_start = __popcll(__ballot(has));
-    const int pass = long_queue ? (flights_per_pass + 1) / 2 : flights_per_pass;
-    const int limit = n_start <= kFewLanes && !__ballot(claim != kNone) ? kFewPass * pass : pass;
+    const int pass = pass_flights(flights_per_pass, long_queue);
+    const int limit = pass_limit(pass, n_start <= kFewLanes && !__ballot(claim != kNone));
     for (int f = 0; f < limit;) {
       const uint64_t m = __ballot(r == STEP_CONTINUE);
       if (!m || (f >= pass && __popcll(m) != n_start)) break;
@@ -1154,6 +1153,7 @@ hipError_t launch_persistent(int fp32, int banded, int field_kind, const GasDev&
                              hipStream_t st) {
   SignalDev Q{};
   if (signal) Q = *signal;
+  flights_per_pass = clamp_flights_per_pass(flights_per_pass);
   const void* fn = pick_persistent(fp32, banded, field_kind, signal != nullptr, tables_fit_lds(G));
   void* args[] = {const_cast<GasDev*>(&G), const_cast<FieldDev*>(&F), const_cast<RunParams*>(&P),
                   const_cast<Store**>(&S), &ctr, &flights_per_pass, &Q};
