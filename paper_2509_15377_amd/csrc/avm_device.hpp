@@ -1582,11 +1582,9 @@ AVM_FN int32_t flight_step(Elec<R>& e, const GasDev& G, const TV& T, const Field
         R mg = Mr::abs_(r_sel - nu_tot);
         const R dm = Mr::abs_(r_sel - c0);
         mg = hit & (dm < mg) ? dm : mg;
-        bool wc = false;
-        first = first & (en > R(1e-30));  // near zero energy its window's edge may be close
+        bool wc = en <= R(kCloseRel * 1e-30);  // at rest the edge of channel 0's window is close (in_window)
         if (hit & !first) {
-          // (at rest also an electron whose r_sel is below c0 comes here)
-          c = select_channel<R>(G, T.el0 & !(r_sel < c0), kb, f, R(1) - f, over, r_sel, mg);
+          c = select_channel<R>(G, T.el0, kb, f, R(1) - f, over, r_sel, mg);
           const ChanP<R> cw = chan(G, T, c);
           c = in_window(cw.e_lo, cw.e_hi, (double)en, c, wc);
         }
