@@ -85,11 +85,26 @@ struct Counters {
   alignas(256) unsigned long long qhead;  // batched: queue entries claimed by lanes
   alignas(256) unsigned long long qtail;  // batched: queue entries published or being published
   alignas(256) unsigned long long ended;  // batched: electrons terminated or dropped, as flushed by waves
-  alignas(256) unsigned long long busy;   // batched: waves that carry electrons
+  alignas(256) unsigned long long load;   // batched: waves that have started (high word), of them with electrons (low)
   alignas(256) unsigned long long next;   // plain: size of the next active list
   unsigned long long err;                 // bad primary avalanche id
   unsigned long long timeout;             // a transport kernel ran out of its time budget
   unsigned long long epoch;               // run counter (bumped by every reset; tags queue entries)
+};
+
+// The rules by which the persistent kernel's waves hand secondaries on, for
+// `waves` of which `busy` carry electrons.  They go by the waves that have
+// started (Counters::load), not by the grid's: with some of the device held
+// by another kernel, or a stream that may use part of it, the rest of the
+// grid only comes when the run is over.
+struct WaveLoad {
+  uint32_t waves, busy;
+  // nearly all carry electrons: a wave may keep its own secondaries
+  AVM_FN bool full() const { return busy * 8u > 7u * waves; }
+  AVM_FN bool spare() const { return busy * 8u < 7u * waves; }
+  // few carry any: secondaries go to waves without (`filled`: these waves
+  // were all full before)
+  AVM_FN bool spread(bool filled) const { return busy * (filled ? 8u : 2u) <= waves; }
 };
 
 struct PrimaryRec {

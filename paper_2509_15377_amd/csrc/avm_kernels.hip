@@ -132,7 +132,7 @@ __global__ void k_reset(Counters* ctr, uint64_t n_prim, AvalStats* stats, uint32
     ctr->qhead = 0;
     ctr->qtail = n_prim;
     ctr->ended = 0;
-    ctr->busy = 0;
+    ctr->load = 0;
     ctr->next = 0;
     ctr->err = 0;
     ctr->timeout = 0;
@@ -423,7 +423,7 @@ AVM_FN void wait_stores() { __builtin_amdgcn_s_waitcnt(0x0F70); /* vmcnt(0) */ }
 // queue.  An atomic on one of the run's counters takes 12 ns whichever wave
 // it comes from, and a claimed record comes after three dependent loads: a
 // wave that hands on and takes single electrons pays both in every pass.
-// While the queue is long (kLongQueue entries per wave) a wave keeps what its
+// While the queue is long (kLongQueue entries per started wave) a wave keeps what its
 // ring holds and claims kReserve entries more than it needs, so most passes
 // touch neither the queue nor another wave; passes are then half as long,
 // which leaves fewer lanes idle behind an ended electron.  With a short queue
@@ -574,14 +574,17 @@ AVM_FN uint32_t draw_ahead(AVM_LDS Xfer* X, bool live, uint64_t m, uint32_t rank
 // ahead by all lanes (RandWave).  An empty wave naps between looks at its
 // claim: up to kIdleMaxNaps x kIdleNap x 64 cycles (1.7 us), kIdlePolls
 // looks between two tests for the run's end.  While at most half of the
-// waves carry electrons and the run has not filled the device yet (7/8 of
-// the waves busy), or at most 1/8 carry some, a wave keeps kSpread electrons
+// waves that have started carry electrons and have not been filled yet (7/8
+// of them busy), or at most 1/8 carry some, a wave keeps kSpread electrons
 // and hands further secondaries to the waves without any: a wave of one
 // electron makes a flight in 0.98 us, one of eight in 1.15, one of 64 in
 // 1.73 (FP64 slab).  Once the device was full, secondaries stay in their
 // wave: spread over waves that share a SIMD they cost more issue slots (1000
-// avalanches 15.8 -> 17.0 ms).  A block's waves come to the queue kStagger
-// naps apart.
+// avalanches 15.8 -> 17.0 ms).  By the grid's waves instead of the started
+// ones (WaveLoad), a run beside a kernel that holds half of the CUs never
+// counts as filled: 1000 avalanches 238 ms against 24, 1024 avalanches of the
+// batched workload 527 against 94.  A block's waves come to the queue
+// kStagger naps apart.
 constexpr int kFewLanes = 32;
 constexpr uint32_t kSpread = 4;
 constexpr int kIdleNap = 16, kIdleMaxNaps = 4, kIdlePolls = 8, kStagger = 4;
@@ -746,7 +749,10 @@ __global__ void __launch_bounds__(kPBlock)
                  int flights_per_pass, SignalDev Q) {
   const uint32_t epoch = (uint32_t)ctr->epoch;
   constexpr unsigned long long kNone = ~0ull;
-  __shared__ Xfer xfer_all[kPBlock / 64];
+  constexpr uint32_t kWaves = kPBlock / 64;
+  if (threadIdx.x == 0)
+    __hip_atomic_fetch_add(&ctr->load, (unsigned long long)kWaves << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __shared__ Xfer xfer_all[kWaves];
   // hot table slices: total rate and cumulative column 0 on the lowest
   // nodes, and the band tables, one copy per block
   constexpr int kLdsNodes = kLdsBytes / (int)sizeof(R);
@@ -755,7 +761,7 @@ __global__ void __launch_bounds__(kPBlock)
   __shared__ ChanP<R> s_ch[kLdsChannels];
   __shared__ double s_sct[2 * kAzN];
   __shared__ unsigned long long s_tally[kTally];
-  __shared__ WaveAcc wacc_all[kPBlock / 64];
+  __shared__ WaveAcc wacc_all[kWaves];
   if (threadIdx.x < kTally) s_tally[threadIdx.x] = 0;
   if ((threadIdx.x & 63u) < 8u) wacc_all[threadIdx.x >> 6].c[threadIdx.x & 63u] = 0ull;
   if ((threadIdx.x & 63u) == 0u) wacc_all[threadIdx.x >> 6].tag = kNoTag;
@@ -788,12 +794,13 @@ __global__ void __launch_bounds__(kPBlock)
   bool has = false, cp = false;
   uint32_t clear = 0;  // the lane's next flight does not end its electron (finish_exit)
   unsigned long long n_gone = 0;  // electrons this wave terminated or dropped, not yet in `ended`
-  bool counted = false;  // this wave carries electrons and is counted in ctr->busy
-  bool filled = false;   // nearly all were at some look
-  const uint32_t n_waves = gridDim.x * (uint32_t)(kPBlock / 64);
-  const uint32_t wave_bits = 31u - (uint32_t)__builtin_clz(n_waves);
+  bool counted = false;  // this wave carries electrons and is counted so in ctr->load
+  // waves the hand-off rules go by: the grid's until this wave has flown (while
+  // the blocks come, the number started says nothing), then those started
+  uint32_t n_waves = gridDim.x * kWaves;
+  uint32_t full_at = 0;  // n_waves at the last look that found nearly all with electrons
   unsigned long long claim = kNone;
-  bool long_queue = false;  // the queue held kLongQueue entries per wave at the last look
+  bool long_queue = false;  // the queue held kLongQueue entries per started wave at the last look
   uint32_t ring_h = 0, ring_n = 0;  // the ring in the transfer buffer: oldest entry, number of entries
   uint64_t ring_born = 0;           // entries born in this wave, whose start is not written yet
   uint32_t slot = 0;
@@ -868,11 +875,13 @@ __global__ void __launch_bounds__(kPBlock)
     // the queue and the other waves, as they are now
     const unsigned long long qt = ld_coh_int(&ctr->qtail);
     const unsigned long long qh = ld_coh_int(&ctr->qhead);
-    const unsigned long long busy = ld_coh_int(&ctr->busy);
+    const unsigned long long ld = ld_coh_int(&ctr->load);
+    if (counted) n_waves = max((uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(ld >> 32)), kWaves);
+    const WaveLoad wl{n_waves, (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)ld)};
     const unsigned long long avail = qt > qh ? qt - qh : 0ull;
     long_queue = avail >= (unsigned long long)kLongQueue * n_waves;
-    filled = filled || busy * 8 > 7ull * n_waves;
-    const bool spread = busy * (filled ? 8 : 2) <= n_waves;
+    if (wl.full()) full_at = n_waves;
+    const bool spread = wl.spread(full_at == n_waves);
     // 2. secondaries wait in the ring; when it is full its newest go to the
     //    queue (they were born here: claimed entries come in only while
     //    kRingClaims are taken at most)
@@ -913,14 +922,15 @@ __global__ void __launch_bounds__(kPBlock)
       uint32_t n_take = n_idle - n_held + (long_queue ? kReserve : 0u);
       n_take = min(n_take, 64u - n_held);
       if (spread) n_take = min(n_take, room);
-      // a wave without an electron takes the share of one in 1/4 of the waves,
+      // a wave without an electron takes the share of one in 1/4 of the started waves,
       // rounded up: a short queue still goes one by one to waves of their own,
       // a longer one to a wave per SIMD.  With one electron for each of more
       // waves the SIMDs' issue slots run out at waves a third full (the whole
       // shares against these, FP64 wire chamber: 2048 electrons 473 -> 345 ms,
       // 1200 296 -> 268, 512 and 64 the same, shares of 1/64 of the waves
       // 5 % slower there; 1000 avalanches the same)
-      const unsigned long long share = n_idle == 64u && ring_n == 0u ? (avail >> (wave_bits - 2u)) + 1ull : avail;
+      const unsigned long long share =
+          n_idle == 64u && ring_n == 0u ? (avail >> (29u - (uint32_t)__builtin_clz(n_waves))) + 1ull : avail;
       n_take = share < n_take ? (uint32_t)share : n_take;
       if (n_take) {
         const uint32_t rk = mask_rank(m_free);
@@ -970,7 +980,7 @@ __global__ void __launch_bounds__(kPBlock)
     ring_n -= n_pop;
     wave_fence();
     // 6. what is left goes to waves without work, if there are any
-    const uint32_t keep = busy * 8 < 7ull * n_waves ? 0u : long_queue ? 64u : kKeep;
+    const uint32_t keep = wl.spare() ? 0u : long_queue ? 64u : kKeep;
     if (ring_n > keep) {
       const uint32_t k = min(born_last(ring_born, ring_h, ring_n), ring_n - keep);
       if (k) publish(S, X, ctr, ring_h + ring_n - k, k, epoch);
@@ -1003,7 +1013,7 @@ __global__ void __launch_bounds__(kPBlock)
       if (lane == 0) {
         if (!claims)
           claim = __hip_atomic_fetch_add(&ctr->qhead, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (counted) __hip_atomic_fetch_add(&ctr->busy, ~0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (counted) __hip_atomic_fetch_add(&ctr->load, ~0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
       counted = false;
       for (int i = 0; i < kIdlePolls; ++i) {
@@ -1015,7 +1025,7 @@ __global__ void __launch_bounds__(kPBlock)
       __builtin_amdgcn_s_setprio(2);
 #endif
       if (!counted && lane == 0)
-        __hip_atomic_fetch_add(&ctr->busy, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_add(&ctr->load, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       counted = true;
     }
   }
