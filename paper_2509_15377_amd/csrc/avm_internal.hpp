@@ -107,6 +107,26 @@ struct WaveLoad {
   AVM_FN bool spread(bool filled) const { return busy * (filled ? 8u : 2u) <= waves; }
 };
 
+// Electrons that a wave keeps while few waves carry any.
+constexpr uint32_t kSpread = 4;
+
+// First claims of the persistent kernel: every block that starts takes its
+// share of the queue, at most `most` entries, with one atomic, and its waves
+// take wave_share() of it each, in order, until it is used up.
+// `n`, `left`: entries published, and not claimed yet (> 0), as it finds them.
+AVM_FN uint32_t least(uint32_t a, uint32_t b) { return a < b ? a : b; }
+AVM_FN uint32_t block_share(uint32_t n, uint32_t left, uint32_t blocks, uint32_t most) {
+  return least(least((n - 1u) / blocks + 1u, left), most);
+}
+// One in 1/4 of the waves (one per SIMD), rounded up, of n entries for
+// `waves` >= 4 waves: four waves take a block's share, unless it is more than
+// their lanes, so that many electrons of few flights cost few atomics (with
+// kSpread a wave, 10000 electrons of four flights 173 us, so 125; of 200
+// flights 402 and 332).  (n < waves: at most kSpread.)
+AVM_FN uint32_t wave_share(uint32_t n, uint32_t waves) {
+  return least((n >> (29u - (uint32_t)__builtin_clz(waves))) + 1u, n >= waves ? 64u : kSpread);
+}
+
 struct PrimaryRec {
   double x, y, z, t, e, dx, dy, dz;
   uint32_t aval, _pad;

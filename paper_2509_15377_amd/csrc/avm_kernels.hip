@@ -430,8 +430,9 @@ AVM_FN void wait_stores() { __builtin_amdgcn_s_waitcnt(0x0F70); /* vmcnt(0) */ }
 // the ring keeps kKeep of the wave's own secondaries, and none while other
 // waves have no work.  The newest leave first; only secondaries born here
 // are published, so an electron is published once at most and the queue needs
-// no more entries than the run holds electrons: claimed entries come in only
-// while the ring holds fewer than kRingClaims.  Same box: 8192 avalanches
+// no more entries than the run holds electrons.  Claimed entries come in for
+// the idle lanes and up to kRingClaims; lanes that are idle then take some at
+// once, so a full ring's newest entry was born here.  Same box: 8192 avalanches
 // 460 -> 414 ms (FP32-mixed 369 -> 312), high gain of 64 avalanches 33.2 ->
 // 29.5 ms (28.0 -> 23.6), 1000 avalanches 16.1 -> 15.6 ms.
 constexpr uint32_t kLongQueue = 4, kKeep = 8, kReserve = 24, kRingClaims = 56;
@@ -583,11 +584,21 @@ AVM_FN uint32_t draw_ahead(AVM_LDS Xfer* X, bool live, uint64_t m, uint32_t rank
 // avalanches 15.8 -> 17.0 ms).  By the grid's waves instead of the started
 // ones (WaveLoad), a run beside a kernel that holds half of the CUs never
 // counts as filled: 1000 avalanches 238 ms against 24, 1024 avalanches of the
-// batched workload 527 against 94.  A block's waves come to the queue
-// kStagger naps apart.
+// batched workload 527 against 94.  With a long queue there is nothing to
+// spread, and four electrons a wave cost an atomic each (1e6 electrons of four
+// flights 1445 -> 1281 us).
+//
+// First claims come by block and by group of kClaimGroup waves, a group's
+// kClaimNaps naps after the one before: with one atomic of 12 ns for each of
+// 4096 waves, in the order of the waves (up to 60 us after the kernel's
+// start), 100 electrons of four flights took 165 us, so 64; 30000 420 and 130;
+// 251 avalanches 9.2 -> 8.8 ms.  Idle waves that claim only when the queue
+// shows an entry come too late: a wave in mid-flight has taken it (251
+// avalanches 10.6 ms).
 constexpr int kFewLanes = 32;
-constexpr uint32_t kSpread = 4;
-constexpr int kIdleNap = 16, kIdleMaxNaps = 4, kIdlePolls = 8, kStagger = 4;
+constexpr int kIdleNap = 16, kIdleMaxNaps = 4, kIdlePolls = 8;
+constexpr uint32_t kClaimGroup = 4, kClaimNaps = 8;
+static_assert(kPBlock / 64 % kClaimGroup == 0, "whole groups");
 
 // ---------------------------------------------------------------------------
 // plain mode: one transport iteration of the paper's loop (Fig. 2)
@@ -724,13 +735,14 @@ __global__ void __launch_bounds__(kBlock) k_generation(GasDev G, FieldDev F, Run
 //      device-coherent, then the entries' ready words after the record
 //      stores are acknowledged);
 //   3. claims queue entries for the idle lanes the ring leaves (one atomic on
-//      qhead) and loads entries whose ready word shows the run's epoch into
-//      the ring; without an electron it takes its share of the queue, or
-//      claims one entry yet to be published and waits at its ready word;
+//      qhead; the block's waves start with claims taken together) and loads
+//      entries whose ready word shows the run's epoch into the ring; without
+//      an electron it takes its share of the queue, or claims one entry yet to
+//      be published and waits at its ready word;
 //   4. counts its terminated (and dropped) electrons locally;
 //   5. lets its idle lanes take the ring's oldest entries (ballot/mbcnt
 //      ranks: the k-th idle lane takes the k-th entry), as many as it keeps
-//      (kSpread while few waves carry electrons);
+//      (kSpread, or what it claimed, while few waves carry electrons);
 //   6. publishes what the ring should not keep.
 // A wave that holds no electron adds its local count to `ended` (one
 // atomic), so `ended` never exceeds the number of electrons terminated.
@@ -750,8 +762,20 @@ __global__ void __launch_bounds__(kPBlock)
   const uint32_t epoch = (uint32_t)ctr->epoch;
   constexpr unsigned long long kNone = ~0ull;
   constexpr uint32_t kWaves = kPBlock / 64;
-  if (threadIdx.x == 0)
+  // the block counts its waves and claims its share of the queue: a claim is
+  // only ever taken by a block that runs (blocks that wait for a CU hold none)
+  __shared__ unsigned long long s_first;
+  __shared__ uint32_t s_share[2];  // entries claimed, and of them for one wave
+  __shared__ unsigned long long s_group[kWaves / kClaimGroup];
+  if (threadIdx.x < kWaves / kClaimGroup) s_group[threadIdx.x] = 0;
+  if (threadIdx.x == 0) {
     __hip_atomic_fetch_add(&ctr->load, (unsigned long long)kWaves << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t qt = (uint32_t)ld_coh_int(&ctr->qtail), qh = (uint32_t)min(ld_coh_int(&ctr->qhead), 0xFFFFFFFFull);
+    const uint32_t n = qt > qh ? block_share(qt, qt - qh, gridDim.x, (uint32_t)kPBlock) : 0u;
+    s_first = n ? __hip_atomic_fetch_add(&ctr->qhead, (unsigned long long)n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
+    s_share[0] = n;
+    s_share[1] = wave_share(qt, gridDim.x * kWaves);
+  }
   __shared__ Xfer xfer_all[kWaves];
   // hot table slices: total rate and cumulative column 0 on the lowest
   // nodes, and the band tables, one copy per block
@@ -806,10 +830,30 @@ __global__ void __launch_bounds__(kPBlock)
   uint32_t slot = 0;
   Elec<R> e;
   Child<R> child;
-  // a block's waves come to the queue one after the other, so that few
-  // primaries spread over all CUs (a claim is only ever taken by a wave that
-  // runs: blocks that wait for a CU hold none)
-  for (uint32_t i = 0; i < (threadIdx.x >> 6) * kStagger; ++i) __builtin_amdgcn_s_sleep(kIdleNap);
+  {
+    const uint32_t w = threadIdx.x >> 6, n = s_share[0], s = s_share[1], i = w * s + lane;
+    if (lane < s && i < n) claim = s_first + i;
+    // The waves left without any hold one claim each, so that the next
+    // entries published come to them and not to a wave in mid-flight.  The
+    // last wave of a group claims for it; the groups come one after the other,
+    // after the blocks' shares, so that the entries go round the CUs.
+    const uint32_t used = (n + s - 1u) / s, group = w / kClaimGroup;
+    if (w >= used) {
+      for (uint32_t j = 0; j < (group + 1u) * kClaimNaps; ++j) __builtin_amdgcn_s_sleep(kIdleNap);
+      const uint32_t last = group * kClaimGroup + kClaimGroup - 1u, from = max(used, group * kClaimGroup);
+      AVM_LDS unsigned long long* at = (AVM_LDS unsigned long long*)&s_group[group];  // its first claim, plus one
+      if (w == last && lane == 0)
+        __hip_atomic_store(at, __hip_atomic_fetch_add(&ctr->qhead, (unsigned long long)(last + 1u - from), __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_AGENT) + 1ull,
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      // (the last wave is without any too, so it comes)
+      unsigned long long b;
+      while ((b = __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) == 0ull)
+        __builtin_amdgcn_s_sleep(1);
+      if (lane == 0) claim = b - 1ull + (w - from);
+    }
+  }
+  bool first = true;  // first visit: the queue is left to the blocks that come
   const uint64_t t_start = wall_clock64();
   for (;;) {
     if (wall_clock64() - t_start > P.budget_ticks) {
@@ -881,10 +925,9 @@ __global__ void __launch_bounds__(kPBlock)
     const unsigned long long avail = qt > qh ? qt - qh : 0ull;
     long_queue = avail >= (unsigned long long)kLongQueue * n_waves;
     if (wl.full()) full_at = n_waves;
-    const bool spread = wl.spread(full_at == n_waves);
+    const bool spread = !long_queue && wl.spread(full_at == n_waves);
     // 2. secondaries wait in the ring; when it is full its newest go to the
-    //    queue (they were born here: claimed entries come in only while
-    //    kRingClaims are taken at most)
+    //    queue (at least the last one was born here)
     if (stored) {
       S.e0[cs] = (double)child.e;
       S.parent[cs] = e.eid;
@@ -918,7 +961,7 @@ __global__ void __launch_bounds__(kPBlock)
     const uint32_t n_has = 64u - n_idle, room = !spread ? 64u : n_has < kSpread ? kSpread - n_has : 0u;
     const uint64_t m_free = __ballot(claim == kNone);
     const uint32_t n_held = ring_n + 64u - __popcll(m_free);
-    if (n_held < n_idle && avail) {
+    if (n_held < n_idle && avail && !first) {
       uint32_t n_take = n_idle - n_held + (long_queue ? kReserve : 0u);
       n_take = min(n_take, 64u - n_held);
       if (spread) n_take = min(n_take, room);
@@ -944,9 +987,11 @@ __global__ void __launch_bounds__(kPBlock)
     }
     //    claimed entries that are published come into the ring
     if (__ballot(claim != kNone)) {
+      // (kRingClaims of them may stay after the idle lanes have taken theirs)
+      const uint32_t most = min(64u, kRingClaims + n_idle);
       const uint64_t m_ready = __ballot(claim < S.capacity && ld_coh_int(&S.qready[claim]) == epoch);
       const uint32_t rk = mask_rank(m_ready);
-      const uint32_t n_ready = min((uint32_t)__popcll(m_ready), ring_n < kRingClaims ? kRingClaims - ring_n : 0u);
+      const uint32_t n_ready = min((uint32_t)__popcll(m_ready), ring_n < most ? most - ring_n : 0u);
       if ((m_ready >> lane & 1) && rk < n_ready) {
         const uint32_t i = (ring_h + ring_n + rk) & 63u, s = ld_coh_int(&S.qslot[claim]);
         X.slot[i] = s;
@@ -962,7 +1007,9 @@ __global__ void __launch_bounds__(kPBlock)
     }
     wave_fence();
     // 5. idle lanes take the ring's oldest entries
-    const uint32_t n_pop = min(min(n_idle, ring_n), room);
+    //    (claimed ones however few the wave is to keep)
+    const uint32_t n_claimed = ring_n - (uint32_t)__popcll(ring_born & ring_bits(ring_h, ring_n));
+    const uint32_t n_pop = min(min(n_idle, ring_n), max(room, n_claimed));
     const uint32_t rank_i = mask_rank(m_idle);
     if (!has && rank_i < n_pop) {
       const uint32_t i = (ring_h + rank_i) & 63u;
@@ -1028,6 +1075,7 @@ __global__ void __launch_bounds__(kPBlock)
         __hip_atomic_fetch_add(&ctr->load, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       counted = true;
     }
+    first = false;
   }
   // (out of time) electrons still in the ring: their starts
   if (lane < ring_n) {
