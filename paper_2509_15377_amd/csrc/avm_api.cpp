@@ -514,12 +514,7 @@ avm_status avm_field_slab(int32_t device, double z_lo_cm, double z_hi_cm, uint32
   D.n_E = n_E;
   D.z_lo = z_lo_cm;
   D.z_hi = z_hi_cm;
-  // the flight filter's half width, less a margin that covers the rounding
-  // of a flight's positions (double, and displacements in single precision)
-  const double half = 0.5 * (z_hi_cm - z_lo_cm), coord = std::fabs(z_lo_cm) + std::fabs(z_hi_cm);
-  D.z_mid = z_lo_cm + half;
-  D.z_half = half - (1e-9 * half + 1e-11 * coord);
-  D.z_half_f = half - (1e-5 * half + 1e-11 * coord);
+  set_slab_filter(D);
   D.E = f->E;
   set_bfield(f, B_T);
   *out = f;

@@ -1352,6 +1352,16 @@ AVM_FN bool slab_clear(const FieldDev& F, double z0, double z1, R w) {
   return (__builtin_fma(0.5, fabs((double)w), fabs(z0 - F.z_mid)) < half) & (fabs(z1 - F.z_mid) < half);
 }
 
+// A slab's middle and half widths for slab_clear(), by precision: less a margin
+// that covers the rounding of a flight's positions (double, and displacements
+// in single precision).  Host side, once per field.
+inline void set_slab_filter(FieldDev& F) {
+  const double half = 0.5 * (F.z_hi - F.z_lo), coord = fabs(F.z_lo) + fabs(F.z_hi);
+  F.z_mid = F.z_lo + half;
+  F.z_half = half - (1e-9 * half + 1e-11 * coord);
+  F.z_half_f = half - (1e-5 * half + 1e-11 * coord);
+}
+
 // One pass of the loop for electron `e`.  Returns STEP_CONTINUE when the
 // electron flies on; STEP_IONISED (with the channel and energy in `child`)
 // when the collision is an ionisation -- the caller then finishes it with
