@@ -187,7 +187,7 @@ typedef enum {
 typedef struct {
   uint64_t seed;          /* Philox key                                                  */
   int32_t precision;      /* avm_precision                                               */
-  int32_t majorant;       /* avm_majorant (banded needs B = 0 and band_bins > 0)          */
+  int32_t majorant;       /* avm_majorant (banded needs band_bins > 0, and in a slab B = 0) */
   int32_t mode;           /* avm_mode                                                    */
   int32_t flights_per_pass; /* batched: flights between queue visits (half as many while   */
                           /*   the queue is long, up to four times as many in a wave of  */

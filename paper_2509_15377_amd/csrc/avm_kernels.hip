@@ -578,8 +578,8 @@ AVM_FN uint32_t draw_ahead(AVM_LDS Xfer* X, bool live, uint64_t m, uint32_t rank
 // waves that have started carry electrons and have not been filled yet (7/8
 // of them busy), or at most 1/8 carry some, a wave keeps kSpread electrons
 // and hands further secondaries to the waves without any: a wave of one
-// electron makes a flight in 0.98 us, one of eight in 1.15, one of 64 in
-// 1.73 (FP64 slab).  Once the device was full, secondaries stay in their
+// electron makes a flight in 0.84 us, one of eight in 1.15, one of 60 in 1.50
+// (FP64 slab, a wave per SIMD).  Once the device was full, secondaries stay in their
 // wave: spread over waves that share a SIMD they cost more issue slots (1000
 // avalanches 15.8 -> 17.0 ms).  By the grid's waves instead of the started
 // ones (WaveLoad), a run beside a kernel that holds half of the CUs never
@@ -610,9 +610,10 @@ static_assert(kPBlock / 64 % kClaimGroup == 0, "whole groups");
 //
 // A wave takes `per_wave` electrons: an iteration lasts as long as its longest
 // chain of flights, and waves of few electrons make a flight in half the time
-// (RandWave), so a short list is spread over the device (launch_generation).
-// 100 avalanches, argon-like gas, banded: 55 -> 31 ms for the run; 1000 avalanches on
-// the global majorant 1606 -> 745 ms.
+// (RandWave), so a short list is spread over the device (gen_one).  Execute to
+// sync, argon-like gas, against full waves that draw in each flight, with the
+// longer flight step of that kernel: 100 avalanches, banded, 24 iterations
+// 67 -> 32 ms; 1000 avalanches 111 -> 62, on the global majorant 1697 -> 759.
 template <class R, bool kBanded, int kField>
 __global__ void __launch_bounds__(kBlock) k_generation(GasDev G, FieldDev F, RunParams P,
                                                        const Store* __restrict__ Sg,
