@@ -592,12 +592,13 @@ AVM_FN uint32_t draw_ahead(AVM_LDS Xfer* X, bool live, uint64_t m, uint32_t rank
 // kClaimNaps naps after the one before: with one atomic of 12 ns for each of
 // 4096 waves, in the order of the waves (up to 60 us after the kernel's
 // start), 100 electrons of four flights took 165 us, so 64; 30000 420 and 130;
-// 251 avalanches 9.2 -> 8.8 ms.  Idle waves that claim only when the queue
+// 251 avalanches 9.2 -> 8.7 ms.  Naps of 3 / 5 / 8: 1000 avalanches 15.31 /
+// 15.28 / 15.74 ms, 251 8.79 / 8.69 / 8.74.  Idle waves that claim only when the queue
 // shows an entry come too late: a wave in mid-flight has taken it (251
 // avalanches 10.6 ms).
 constexpr int kFewLanes = 32;
 constexpr int kIdleNap = 16, kIdleMaxNaps = 4, kIdlePolls = 8;
-constexpr uint32_t kClaimGroup = 4, kClaimNaps = 8;
+constexpr uint32_t kClaimGroup = 4, kClaimNaps = 5;
 static_assert(kPBlock / 64 % kClaimGroup == 0, "whole groups");
 
 // ---------------------------------------------------------------------------
