@@ -189,10 +189,11 @@ typedef struct {
   int32_t precision;      /* avm_precision                                               */
   int32_t majorant;       /* avm_majorant (banded needs band_bins > 0, and in a slab B = 0) */
   int32_t mode;           /* avm_mode                                                    */
-  int32_t flights_per_pass; /* batched: flights between queue visits (half as many while   */
-                          /*   the queue is long, up to four times as many in a wave of  */
-                          /*   few electrons while none of them stops; above 2^28 as     */
-                          /*   2^28); results do not depend on it; 0: 48                 */
+  int32_t flights_per_pass; /* batched: flights between queue visits (banded: half as many */
+                          /*   while the queue is long; up to four times as many in a    */
+                          /*   wave of few electrons, on the global majorant also in a   */
+                          /*   full one, while none of them stops; above 2^28 as 2^28);  */
+                          /*   results do not depend on it; 0: 48                        */
   double t_max_ns;        /* time limit (INFINITY: none) -> status 6                     */
   uint64_t capacity;      /* electrons the run can hold (primaries included), >= n_prim  */
   uint32_t k_max;         /* flights per electron before status 7; 0: 2^30-1             */
